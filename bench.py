@@ -29,9 +29,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
-# translation units each fused kernel is built from (the _dflt and _f64r3
-# units include the kernel file and build some of its instantiations)
-KERNEL_SOURCE = {"split": ("rk3_split.hip", "rk3_split_f64r3.hip", "rk3_split_dflt.hip"),
+# translation units each fused kernel is built from (the _dflt unit includes
+# the kernel file and builds some of its instantiations)
+KERNEL_SOURCE = {"split": ("rk3_split.hip",),
                  "tiled": ("rk3_tiled.hip", "rk3_tiled_dflt.hip"), "direct": ("rk3_direct.hip",)}
 KERNEL_SYMBOL = {"split": "k_rk3_split", "tiled": "k_rk3_tiled", "direct": "k_rk3_direct"}
 

@@ -34,6 +34,10 @@ struct Prec<MHD_F32> {
     using D2 = float;
 };
 
+// a * b + c with one rounding.
+__device__ __forceinline__ double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
 // First derivative times h along a stride st (radius RAD).
 template <typename A, int RAD, typename T>
 __device__ __forceinline__ A deriv1(const T* p, int st)
