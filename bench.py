@@ -29,11 +29,11 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
-# translation units each fused kernel is built from (the _dflt unit includes
-# the kernel file and builds some of its instantiations)
-KERNEL_SOURCE = {"split": ("rk3_split.hip",),
-                 "tiled": ("rk3_tiled.hip", "rk3_tiled_dflt.hip"), "direct": ("rk3_direct.hip",)}
-KERNEL_SYMBOL = {"split": "k_rk3_split", "tiled": "k_rk3_tiled", "direct": "k_rk3_direct"}
+# sources of each fused kernel: the translation unit of its precision and the
+# kernel's own header (split and tiled name one kernel)
+KERNEL_SOURCE = {"split": ("rk3_split.hip", "rk3_march.hpp"),
+                 "tiled": ("rk3_tiled.hip", "rk3_march.hpp"), "direct": ("rk3_direct.hip",)}
+KERNEL_SYMBOL = {"split": "k_rk3_split", "tiled": "k_rk3_split", "direct": "k_rk3_direct"}
 
 WORKLOAD_TEXT = {
     "prec512": "prec512: 512^3 periodic, 8 fields, 1e-2 x 4 Fourier modes |k|<=8 seed 3, "

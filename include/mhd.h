@@ -73,12 +73,13 @@ enum mhd_reduce_op {
 
 /* ---------------------------------------------------------------- types */
 /* Which fused-substep kernel runs (same results up to rounding order).
+ * TILED and SPLIT name the same LDS-tiled kernel, the fastest one at every
+ * order and precision.
  * All three serve every order and precision.
- * AUTO: init picks the fastest for the precision and order (SPLIT for
- * MHD_F64 at every order and for MHD_F32C / MHD_F32 at order 8, TILED
- * otherwise) and reports it in mhd_layout.kernel. */
+ * AUTO: init picks it and reports SPLIT in mhd_layout.kernel for MHD_F64 at
+ * every order and for MHD_F32C / MHD_F32 at order 8, TILED otherwise. */
 enum mhd_kernel {
-    MHD_KERNEL_TILED = 0,  /* LDS-tiled z-marching kernel */
+    MHD_KERNEL_TILED = 0,  /* LDS-tiled z-marching kernel (as SPLIT) */
     MHD_KERNEL_DIRECT = 1, /* one thread per cell, stencil read from global memory */
     MHD_KERNEL_SPLIT = 2,  /* LDS-tiled z-march, two threads per cell splitting the
                               fields (velocity side / entropy-induction side) */

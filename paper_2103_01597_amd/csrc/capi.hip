@@ -13,10 +13,7 @@ namespace mhd {
 hipError_t launch_rk3_direct(const Grid& g, const Phys& P, int precision, const Box& bx, int s,
                              const void* f_in, void* f_out, void* w, void* comp, double dt,
                              hipStream_t st);
-hipError_t launch_rk3_tiled(const Grid& g, const Phys& P, int precision, const Box* bx, int nbox,
-                            int s, const void* f_in, void* f_out, void* w, void* comp, double dt,
-                            hipStream_t st);
-hipError_t launch_rk3_split(const Grid& g, const Phys& P, const Phys* P_dev, int precision,
+hipError_t launch_rk3_march(const Grid& g, const Phys& P, const Phys* P_dev, int precision,
                             const Box* bx, int nbox, int s, const void* f_in, void* f_out,
                             void* w, void* comp, double dt, hipStream_t st);
 }  // namespace mhd
@@ -108,18 +105,12 @@ int one_substep(mhd_ctx* ctx, int s, const Box* boxes, int nbox, const void* f_i
     const Grid& g = ctx->grid;
     const int prec = ctx->cfg.precision;
     hipError_t e = hipSuccess;
-    switch (ctx->cfg.kernel) {
-    case MHD_KERNEL_TILED:
-        e = launch_rk3_tiled(g, ctx->phys, prec, bx, n, s, f_in, f_out, w, comp, dt, st);
-        break;
-    case MHD_KERNEL_SPLIT:
-        e = launch_rk3_split(g, ctx->phys, ctx->phys_dev, prec, bx, n, s, f_in, f_out, w, comp,
-                             dt, st);
-        break;
-    default:
+    if (ctx->cfg.kernel == MHD_KERNEL_DIRECT) {
         for (int k = 0; k < n && e == hipSuccess; ++k)
             e = launch_rk3_direct(g, ctx->phys, prec, bx[k], s, f_in, f_out, w, comp, dt, st);
-        break;
+    } else {
+        e = launch_rk3_march(g, ctx->phys, ctx->phys_dev, prec, bx, n, s, f_in, f_out, w, comp, dt,
+                             st);
     }
     return from_hip(e);
 }
@@ -302,9 +293,8 @@ int mhd_init(const mhd_config* cfg, mhd_ctx** out, mhd_layout* layout)
     ctx->cfg = *cfg;
     ctx->device = dev;
 
-    // AUTO: the fastest kernel built for the precision and order (measured
-    // at 512^3 and 256^3 on MI355X): SPLIT for FP64 at every order and for
-    // the FP32 variants at order 8, TILED otherwise
+    // AUTO reports SPLIT for FP64 at every order and for the FP32 variants at
+    // order 8, TILED otherwise; one kernel serves both
     if (cfg->kernel == MHD_KERNEL_AUTO) {
         const bool split = cfg->precision == MHD_F64 || cfg->order == 8;
         ctx->cfg.kernel = split ? MHD_KERNEL_SPLIT : MHD_KERNEL_TILED;

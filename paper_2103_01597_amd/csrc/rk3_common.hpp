@@ -38,6 +38,30 @@ struct Prec<MHD_F32> {
 __device__ __forceinline__ double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
+// Values computed here and nowhere later: without this the compiler moves a
+// phase's arithmetic past the scheduling fences, down to its use behind the
+// barrier, and keeps the stencil's LDS reads in registers until then (spills).
+template <typename... A>
+__device__ __forceinline__ void pin(A&... a)
+{
+    (..., [](auto& x) { asm volatile("" : "+v"(x)); }(a));
+}
+
+// A field's LDS reads for one step of the derivative phase ([0]: the lower, [1]:
+// the upper side of the cell; m - 1).
+template <typename T, int RAD>
+struct LineA {
+    T x[2][RAD], y[2][RAD], z[RAD], c;
+};
+template <typename T, int RAD>
+struct LineB {
+    T d[4][RAD], f[2][RAD];
+};
+template <typename T, int RAD>
+struct LineC {
+    T fx[2][RAD], fy[2][RAD];
+};
+
 // First derivative times h along a stride st (radius RAD).
 template <typename A, int RAD, typename T>
 __device__ __forceinline__ A deriv1(const T* p, int st)
