@@ -31,6 +31,7 @@
 // derivatives; those go through LDS:
 //   F -> M (5 values): grad lnrho, lap lnrho, the viscous heating;
 //   M -> F (4 values): the force j x B / rho - cs^2 grad s / cp, and cs^2
+// (FP32 storage: 6 and 6 values, see physics_late).
 // (M reads lnrho and u themselves from the ring).  A plane costs two barriers:
 //   derivatives and own equations of plane t, the loads of plane t+r+1 issued
 //   between their first steps; both groups write their values
@@ -52,7 +53,7 @@
 // (7.8-7.9 ms), nor do wave priorities; non-temporal stores cost 6%.
 // With FP32 storage one thread per cell for all 8 fields, two workgroups to a
 // CU, took 22.6 ms per step at 512^3, sixth order (21.8 at orders 2 and 4); the
-// two groups take 20.8 (18.7, 19.1) although only one workgroup is resident.
+// two groups take 20.2 (18.6, 19.3) although only one workgroup is resident.
 #pragma once
 
 #include <type_traits>
@@ -64,8 +65,20 @@ namespace mhd {
 
 namespace {
 
-constexpr int NXF = 5;             // values F hands to M
-constexpr int NXM = 4;             // values M hands to F
+// Whether each group evaluates all of its equations after the hand-over, from
+// the other's derivatives, rather than its own terms before it.  FP32 storage
+// does: the terms are then rounded and added as in every other kernel of the
+// library (rhs_flow, rhs_entropy_induction), while in FP64 a term's rounding is
+// far below what a caller can see, and the shorter hand-over pays (512^3: 17
+// values 8.2, 9 values 7.9 ms per substep).  With its terms handed over like
+// those of FP64, one step of FP32C at 512^3 changed 40% of the register values
+// by a rounding; now four of the eight fields keep every bit.
+template <int PREC>
+constexpr bool physics_late() { return PREC != MHD_F64; }
+template <int PREC>
+constexpr int nxf() { return physics_late<PREC>() ? 6 : 5; }  // values F hands to M
+template <int PREC>
+constexpr int nxm() { return physics_late<PREC>() ? 6 : 4; }  // values M hands to F
 // Per precision and stencil radius RAD: the tile plane of TX x TY cells
 // (TY = 4 for FP64 at RAD = 4, whose 5-plane ring of a 32 x 8 tile would not
 // fit the LDS; 8 otherwise), the halo'd tile plane (38 x 14 = 532 cells at
@@ -94,7 +107,7 @@ template <int PREC, int RAD>
 constexpr size_t lds_bytes()
 {
     constexpr size_t need = ring_bytes<PREC, RAD>() +
-                            sizeof(typename Prec<PREC>::Rt) * (NXF + NXM) * SRing<PREC, RAD>::NC;
+                            sizeof(typename Prec<PREC>::Rt) * (nxf<PREC>() + nxm<PREC>()) * SRing<PREC, RAD>::NC;
     return need > 84 * 1024 ? need : 84 * 1024;
 }
 
@@ -228,6 +241,8 @@ __global__ __launch_bounds__((SRing<PREC, RAD>::NTH), 1) void k_rk3_split(Grid g
     constexpr int TY = RG::TY, NC = RG::NC;
     constexpr int HX = RG::HX, PLANE = RG::PLANE, SLOT = RG::SLOT;
     constexpr int NSLOT = RG::NSLOT;
+    constexpr bool LATE = physics_late<PREC>();
+    constexpr int NXF = nxf<PREC>(), NXM = nxm<PREC>();
 
     const int tile = MULTI ? multi_tile : tile_of_block(blockIdx.x, map);
     if (tile == NO_TILE) return;  // the whole workgroup exits together
@@ -412,6 +427,7 @@ __global__ __launch_bounds__((SRing<PREC, RAD>::NTH), 1) void k_rk3_split(Grid g
             T fc[4], wold[4] = {}, cc[4] = {};
             Rt rhs[4];
             EntropyOwn<Rt> own;
+            Rt S[3][3], divu, SS, B[3], J[3];  // LATE only
             {
                 int sl[RAD + 1];  // ring slots of planes t .. t+RAD
 #pragma unroll
@@ -461,7 +477,9 @@ __global__ __launch_bounds__((SRing<PREC, RAD>::NTH), 1) void k_rk3_split(Grid g
                     rdF(L.fx, q, 0);
                     rdF(L.fy, q, 1);
                 };
-                // first derivative along x (0) or y (1), or z (2)
+                // first derivative along x (0) or y (1), or z (2); LATE: not yet scaled
+                // (scaled beside its use, where the compiler fuses the product as
+                // it does in the other kernels)
                 auto first = [&](const LineA<T, RAD>& L, int k4, int dir) -> Rt {
                     auto g1 = [&](int m) -> Rt {
                         if (dir == 2) return Rt(L.z[m - 1]) - Rt(hist[RAD - m][k4]);
@@ -471,7 +489,7 @@ __global__ __launch_bounds__((SRing<PREC, RAD>::NTH), 1) void k_rk3_split(Grid g
                     Rt acc = Rt(W1(RAD, 1)) * g1(1);
 #pragma unroll
                     for (int m = 2; m <= RAD; ++m) acc += Rt(W1(RAD, m)) * g1(m);
-                    return acc * Rt(sc.d1[dir]);
+                    return LATE ? acc : acc * Rt(sc.d1[dir]);
                 };
                 auto second = [&](const LineA<T, RAD>& L, int k4, D2& xx, D2& yy, D2& zz) {
                     const D2 f0 = D2(W2(RAD, 0)) * D2(L.c);
@@ -662,6 +680,8 @@ __global__ __launch_bounds__((SRing<PREC, RAD>::NTH), 1) void k_rk3_split(Grid g
                     d.ux = Rt(V(s0, 1, 0, 0));
                     d.uy = Rt(V(s0, 2, 0, 0));
                     d.uz = Rt(V(s0, 3, 0, 0));
+                } else if constexpr (LATE) {
+                    d.ss = Rt(V(s0, 4, 0, 0));  // and the entropy of group M's
                 }
                 MHD_PHASE_FENCE();
                 grad[0] += future(C3.fx, 0) - mix;
@@ -671,17 +691,44 @@ __global__ __launch_bounds__((SRing<PREC, RAD>::NTH), 1) void k_rk3_split(Grid g
                 if constexpr (G == 0) {
 #pragma unroll
                     for (int a = 0; a < 3; ++a) d.gdu[a] = Rt(grad[a]);
-                    Rt heat;
-                    rhs_flow_own(d, P, rhs, heat);
-                    const Rt v[NXF] = {d.gl[0], d.gl[1], d.gl[2], d.lapl, heat};
+                    if constexpr (LATE) {
+#pragma unroll
+                        for (int b = 0; b < 3; ++b) {
+                            d.gl[b] *= Rt(sc.d1[b]);
+#pragma unroll
+                            for (int a = 0; a < 3; ++a) d.gu[a][b] *= Rt(sc.d1[b]);
+                        }
+                    }
+                    Rt v[NXF] = {d.gl[0], d.gl[1], d.gl[2], d.lapl};
+                    if constexpr (LATE) {
+                        shear(d.gu, S, divu, SS);
+                        v[4] = SS;
+                        v[NXF - 1] = divu;
+                    } else {
+                        rhs_flow_own(d, P, rhs, v[4]);
+                    }
 #pragma unroll
                     for (int i = 0; i < NXF; ++i) xch[i * NC + tid] = v[i];
                 } else {
 #pragma unroll
                     for (int a = 0; a < 3; ++a) d.jmu[a] = Rt(grad[a]);
-                    Rt force[3], cs2;
-                    rhs_entropy_own(d, P, own, rhs, force, cs2);
-                    const Rt v[NXM] = {force[0], force[1], force[2], cs2};
+                    Rt v[NXM];
+                    if constexpr (LATE) {
+                        const Rt sx = Rt(sc.d1[0]), sy = Rt(sc.d1[1]), sz = Rt(sc.d1[2]);
+                        d.dAx_dy *= sy; d.dAx_dz *= sz;
+                        d.dAy_dx *= sx; d.dAy_dz *= sz;
+                        d.dAz_dx *= sx; d.dAz_dy *= sy;
+                        d.gs[0] *= sx; d.gs[1] *= sy; d.gs[2] *= sz;
+                        Rt jxB[3];
+                        magnetic(d, P, B, J, jxB);
+#pragma unroll
+                        for (int a = 0; a < 3; ++a) {
+                            v[a] = d.gs[a];
+                            v[NXM - 3 + a] = jxB[a];
+                        }
+                    } else {
+                        rhs_entropy_own(d, P, own, rhs, v, v[3]);
+                    }
 #pragma unroll
                     for (int i = 0; i < NXM; ++i) xch[(NXF + i) * NC + tid] = v[i];
                 }
@@ -700,7 +747,18 @@ __global__ __launch_bounds__((SRing<PREC, RAD>::NTH), 1) void k_rk3_split(Grid g
             __syncthreads();  // plane t+RAD+1 visible; the hand-over area is free
 
             // The right-hand sides completed, and the 2N update.
-            if constexpr (G == 0) {
+            if constexpr (LATE) {
+                if constexpr (G == 0) {
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) d.gs[a] = in[a];
+                    rhs_flow(d, *P_dev, S, divu, in + 3, rhs);
+                } else {
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) d.gl[a] = in[a];
+                    d.lapl = in[3];
+                    rhs_entropy_induction(d, *P_dev, in[NIN - 1], in[4], B, J, rhs);
+                }
+            } else if constexpr (G == 0) {
 #pragma unroll
                 for (int a = 0; a < 3; ++a) rhs[1 + a] += in[a] - in[3] * d.gl[a];
             } else {
