@@ -169,7 +169,7 @@ __device__ __forceinline__ void rk_update(int s, typename Prec<PREC>::T f_in,
 // tile = (chunk * nty + ty) * ntx + tx.
 constexpr int MAX_BOXES = 6;
 constexpr int NO_TILE = -1;
-constexpr int ZCHUNK_MIN = 16, WARM_PLANES = 7;
+constexpr int START_PLANES = 2;
 
 struct TilePlan {
     int nbox;
@@ -182,14 +182,21 @@ struct TilePlan {
 
 // Z chunks.  The hardware hands workgroups to free slots in launch order,
 // so a launch lasts about the makespan of greedy list scheduling of its
-// chunks (each taking its planes plus the warm-up planes) on the `round`
-// resident slots; tiles are numbered longest chunk first, so that the short
-// chunks (thin slabs) fill the gaps the long ones leave (for one box: whole
-// rounds of equal chunks).  Thin boxes and tile counts just above a whole
-// number of rounds march in the common chunk length Z of least makespan:
-// every box of more than Z planes is cut into chunks of at most Z planes, no
-// chunk below ZCHUNK_MIN planes unless its box is.  Candidates: each box's
-// own length over 1, 2, ... chunks.
+// chunks on the `round` resident slots, each taking its planes plus the start
+// of its march (START_PLANES: filling the ring and the z state from global
+// memory takes about as long as one plane where the chip is idle, 3.0 against
+// 2.9 us, and more under load).  All boxes march in one common chunk length Z,
+// every box of more than Z planes cut into chunks of at most Z, and Z is the
+// one of least makespan; tiles are numbered longest chunk first, so that the
+// short chunks (thin slabs) fill the gaps the long ones leave.
+//
+// One box: whole rounds of equal chunks, so every number of chunks is tried.
+// Grids that leave CUs idle are cut down to single planes (substep, FP64 32^3:
+// chunks of 16 planes 54 us, of 1 plane 11; FP32C 64^3: 16 planes 51, 4 planes
+// 21 us); the others keep whole rounds (151 x 131 x 97: 33 planes 145 us, 11
+// planes 158).  Several boxes: candidates are each box's length over 1, 2, ...
+// chunks of at least 16 planes, and shorter ones as long as all the chunks
+// make no more than four rounds.
 inline int64_t greedy_makespan(int n, const int64_t* jobs, const int* len, int round)
 {
     std::priority_queue<int64_t, std::vector<int64_t>, std::greater<int64_t>> slots;
@@ -229,38 +236,56 @@ inline TilePlan plan_tiles_uncached(const Box* b, int n, int tx, int ty, int rou
                 ord[c - 1] = t;
             }
     };
-    if (round > 0) {
+    if (round > 0 && n == 1) {
         int64_t best = -1;
+        for (int c = 1; c <= nzb[0]; ++c) {
+            const int z = (nzb[0] + c - 1) / c;
+            const int64_t jobs = cols[0] * ((nzb[0] + z - 1) / z);
+            const int64_t cost = (jobs + round - 1) / round * (z + START_PLANES);
+            if (best < 0 || cost < best) {
+                best = cost;
+                zc[0] = z;
+                nch[0] = (nzb[0] + z - 1) / z;
+            }
+        }
+    } else if (round > 0) {
+        int64_t best = -1;
+        auto consider = [&](int Z) {
+            int cn[MAX_BOXES], cz[MAX_BOXES], ord[MAX_BOXES], len[MAX_BOXES];
+            int64_t jobs[MAX_BOXES], total = 0;
+            for (int k = 0; k < n; ++k) {
+                cn[k] = nzb[k] > Z ? (nzb[k] + Z - 1) / Z : 1;
+                cz[k] = (nzb[k] + cn[k] - 1) / cn[k];
+                total += cols[k] * cn[k];
+            }
+            if (Z < 16 && Z < zmax && total > 4 * (int64_t)round) return;
+            order_of(cz, ord);
+            for (int k = 0; k < n; ++k) {
+                jobs[k] = cols[ord[k]] * cn[ord[k]];
+                len[k] = cz[ord[k]] + START_PLANES;
+            }
+            const int64_t cost = greedy_makespan(n, jobs, len, round);
+            if (best < 0 || cost < best) {
+                best = cost;
+                for (int k = 0; k < n; ++k) {
+                    nch[k] = cn[k];
+                    zc[k] = cz[k];
+                }
+            }
+        };
         int tried[64], ntried = 0;
-        for (int want = 1; want == 1 || want <= zmax / ZCHUNK_MIN; ++want) {
+        for (int want = 1; want == 1 || want <= zmax / 16; ++want) {
             for (int j = 0; j < n; ++j) {
-                if (want > 1 && want > nzb[j] / ZCHUNK_MIN) continue;
+                if (want > 1 && want > nzb[j] / 16) continue;
                 const int Z = (nzb[j] + want - 1) / want;
                 bool seen = false;
                 for (int t = 0; t < ntried; ++t) seen |= tried[t] == Z;
                 if (seen) continue;
                 if (ntried < 64) tried[ntried++] = Z;
-                int cn[MAX_BOXES], cz[MAX_BOXES], ord[MAX_BOXES], len[MAX_BOXES];
-                int64_t jobs[MAX_BOXES];
-                for (int k = 0; k < n; ++k) {
-                    cn[k] = nzb[k] > Z ? (nzb[k] + Z - 1) / Z : 1;
-                    cz[k] = (nzb[k] + cn[k] - 1) / cn[k];
-                }
-                order_of(cz, ord);
-                for (int k = 0; k < n; ++k) {
-                    jobs[k] = cols[ord[k]] * cn[ord[k]];
-                    len[k] = cz[ord[k]] + WARM_PLANES;
-                }
-                const int64_t cost = greedy_makespan(n, jobs, len, round);
-                if (best < 0 || cost < best) {
-                    best = cost;
-                    for (int k = 0; k < n; ++k) {
-                        nch[k] = cn[k];
-                        zc[k] = cz[k];
-                    }
-                }
+                consider(Z);
             }
         }
+        for (int Z : {12, 8, 6, 4, 3, 2, 1}) consider(Z);
     }
     int ord[MAX_BOXES];
     order_of(zc, ord);
