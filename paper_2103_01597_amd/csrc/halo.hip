@@ -10,100 +10,89 @@ namespace {
 
 __device__ __forceinline__ int wrap_index(int s, int n, int r)
 {
-    int t = (s - r) % n;
-    return (t < 0 ? t + n : t) + r;
+    int t = s - r;
+    if (n < r) {  // a box thinner than its halo (uniform)
+        t %= n;
+        return (t < 0 ? t + n : t) + r;
+    }
+    return (t < 0 ? t + n : t >= n ? t - n : t) + r;
 }
 
-// Three launches, each reading only cells that are final when it runs:
-//   X: interior planes and rows, the 2r halo columns (element copies of
-//      interior cells, x wrapped);
-//   Y: interior planes, the 2r halo rows, each copied whole (its halo
-//      columns included, filled by X) from the wrapped interior row;
-//   Z: the 2r halo planes, each copied whole from the wrapped interior plane.
-// Y and Z copy whole rows and planes in units of V elements (V = 2 when the
-// padded row length mx is even: every row then starts on a V-element
-// boundary, so FP64 moves 16 bytes per access).
-template <typename E, int V>
-struct alignas(sizeof(E) * V) HVec {
-    E v[V];
-};
-
-// X: a workgroup covers 32 rows of one interior plane of one field, eight
-// lanes per row (lane c < 2r fills column c of the left halo, c < r, or
-// column c - r of the right halo), so the row and plane come from the
-// launch indices rather than from divisions.
-constexpr int HX_ROWS = 32;
+// One launch, every halo cell straight from the interior cell it maps to, so
+// no part waits for another.  Workgroups [0, xblocks) fill the 2r halo columns
+// of the interior rows; the rest copy whole rows of the halo (the 2r halo
+// planes, then the 2r halo rows of the interior planes), x wrapped at both ends.
+//
+// X part: a workgroup covers 32 rows of the interior of one field, eight lanes
+// per row (lane c < 2r fills column c of the left halo, c < r, or column c - r
+// of the right halo).  Bound: the columns touch two cache lines per row for 2r
+// cells.  Row part: consecutive lanes copy consecutive cells.
+constexpr int HX_ROWS = 32, ROW_UNROLL = 4;
 
 template <typename E>
-__global__ __launch_bounds__(256) void k_halo_x(Grid g, E* __restrict__ fields)
+__global__ __launch_bounds__(256) void k_halo(Grid g, unsigned xblocks, int lanes_log2,
+                                                E* __restrict__ fields)
 {
-    const int r = g.r, c = threadIdx.x & 7;
-    const int yy = blockIdx.x * HX_ROWS + (threadIdx.x >> 3);
-    if (c >= 2 * r || yy >= g.ny) return;
-    E* f = fields + (int64_t)blockIdx.z * g.fstride;
-    const int row = ((r + (int)blockIdx.y) * g.my + r + yy) * g.mx;
-    const int dst = c < r ? c : g.nx + c;  // padded halo column
-    f[row + dst] = f[row + wrap_index(dst, g.nx, r)];
-}
-
-template <typename E, int V>
-__global__ __launch_bounds__(256) void k_halo_y(Grid g, E* __restrict__ fields)
-{
-    using Vt = HVec<E, V>;
-    const int r = g.r, row_units = g.mx / V;
-    const int per_plane = 2 * r * row_units;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= g.nz * per_plane) return;
+    const int r = g.r;
     E* f = fields + (int64_t)blockIdx.y * g.fstride;
-    const int zz = t / per_plane, rem = t - zz * per_plane;
-    const int yr = rem / row_units, u = rem - yr * row_units;
-    const int y = yr < r ? yr : g.ny + yr;
-    const int plane = (r + zz) * g.mxy;
-    Vt* dst = reinterpret_cast<Vt*>(f + plane + y * g.mx);
-    const Vt* src = reinterpret_cast<const Vt*>(f + plane + wrap_index(y, g.ny, r) * g.mx);
-    dst[u] = src[u];
+    if (blockIdx.x < xblocks) {
+        const int c = threadIdx.x & 7;
+        if (c >= 2 * r) return;
+        const int dst = c < r ? c : g.nx + c;  // padded halo column
+        const int src = wrap_index(dst, g.nx, r);
+        const int row = (int)blockIdx.x * HX_ROWS + (threadIdx.x >> 3);
+        if (row >= g.ny * g.nz) return;
+        const int z = row / g.ny, y = row - z * g.ny;
+        E* p = f + ((r + z) * g.my + r + y) * g.mx;
+        p[dst] = p[src];
+        return;
+    }
+    // 2^lanes_log2 lanes per row, each copying up to ROW_UNROLL cells of it at once
+    const int lanes = 1 << lanes_log2;
+    int k = (int)(blockIdx.x - xblocks) * (256 >> lanes_log2) + ((int)threadIdx.x >> lanes_log2);
+    int z, y;
+    if (k < 2 * r * g.my) {
+        z = k / g.my;
+        y = k - z * g.my;
+        if (z >= r) z += g.nz;
+    } else {
+        k -= 2 * r * g.my;
+        z = k / (2 * r);
+        y = k - z * (2 * r);
+        if (z >= g.nz) return;
+        z += r;
+        if (y >= r) y += g.ny;
+    }
+    E* dst = f + (z * g.mxy + y * g.mx);
+    const E* src = f + (wrap_index(z, g.nz, r) * g.mxy + wrap_index(y, g.ny, r) * g.mx);
+    for (int x0 = (int)threadIdx.x & (lanes - 1); x0 < g.mx; x0 += ROW_UNROLL * lanes) {
+        E v[ROW_UNROLL];
+#pragma unroll
+        for (int i = 0; i < ROW_UNROLL; ++i)
+            if (x0 + i * lanes < g.mx) v[i] = src[wrap_index(x0 + i * lanes, g.nx, r)];
+#pragma unroll
+        for (int i = 0; i < ROW_UNROLL; ++i)
+            if (x0 + i * lanes < g.mx) dst[x0 + i * lanes] = v[i];
+    }
 }
 
-template <typename E, int V>
-__global__ __launch_bounds__(256) void k_halo_z(Grid g, E* __restrict__ fields)
-{
-    using Vt = HVec<E, V>;
-    const int r = g.r, plane_units = g.mxy / V;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 2 * r * plane_units) return;
-    E* f = fields + (int64_t)blockIdx.y * g.fstride;
-    const int p = t / plane_units, u = t - p * plane_units;
-    const int z = p < r ? p : g.nz + p;
-    Vt* dst = reinterpret_cast<Vt*>(f + z * g.mxy);
-    const Vt* src = reinterpret_cast<const Vt*>(f + wrap_index(z, g.nz, r) * g.mxy);
-    dst[u] = src[u];
-}
-
-template <typename E, int V>
+template <typename E>
 void launch_halo_typed(const Grid& g, void* fields, hipStream_t st)
 {
-    const int w = 2 * g.r;
-    auto blocks = [](int n) { return dim3((unsigned)((n + 255) / 256), NQ); };
-    hipLaunchKernelGGL(k_halo_x<E>, dim3((unsigned)((g.ny + HX_ROWS - 1) / HX_ROWS), (unsigned)g.nz, NQ),
-                       dim3(256), 0, st, g, (E*)fields);
-    hipLaunchKernelGGL((k_halo_y<E, V>), blocks(g.nz * w * (g.mx / V)), dim3(256), 0, st, g,
-                       (E*)fields);
-    hipLaunchKernelGGL((k_halo_z<E, V>), blocks(w * (g.mxy / V)), dim3(256), 0, st, g,
-                       (E*)fields);
+    const unsigned xblocks = (unsigned)(((int64_t)g.ny * g.nz + HX_ROWS - 1) / HX_ROWS);
+    int lg = 5;  // lanes of a row: about a quarter of it, 32 to 256
+    while (lg < 8 && (1 << lg) * ROW_UNROLL < g.mx) ++lg;
+    const int64_t rows = (int64_t)2 * g.r * (g.my + g.nz), per_block = 256 >> lg;
+    hipLaunchKernelGGL(k_halo<E>, dim3(xblocks + (unsigned)((rows + per_block - 1) / per_block), NQ),
+                       dim3(256), 0, st, g, xblocks, lg, (E*)fields);
 }
 
 }  // namespace
 
 hipError_t launch_halo(const Grid& g, void* fields, int elem_size, hipStream_t st)
 {
-    const bool vec = g.mx % 2 == 0;
-    if (elem_size == 8) {
-        if (vec) launch_halo_typed<uint64_t, 2>(g, fields, st);
-        else launch_halo_typed<uint64_t, 1>(g, fields, st);
-    } else {
-        if (vec) launch_halo_typed<uint32_t, 2>(g, fields, st);
-        else launch_halo_typed<uint32_t, 1>(g, fields, st);
-    }
+    if (elem_size == 8) launch_halo_typed<uint64_t>(g, fields, st);
+    else launch_halo_typed<uint32_t>(g, fields, st);
     return hipGetLastError();
 }
 
