@@ -178,9 +178,8 @@ int mhd_rk3_substep(mhd_ctx *ctx, int32_t s, const void *f_in, void *f_out, void
 /* nsteps full RK3 steps (Section 5: each step is three substeps), each
  * substep preceded by mhd_halo_periodic on the current buffer.  Starts
  * from f[*cur] and ping-pongs between f[0] and f[1]; on return *cur names
- * the buffer holding the result (it flips once per step).  Small grids are
- * replayed from a captured HIP graph.  Errors: as mhd_rk3_substep, and
- * MHD_ERR_INVALID for nsteps < 0 or *cur not in {0, 1}. */
+ * the buffer holding the result (it flips once per step).  Errors: as
+ * mhd_rk3_substep, and MHD_ERR_INVALID for nsteps < 0 or *cur not in {0, 1}. */
 int mhd_step(mhd_ctx *ctx, void *const f[2], int32_t *cur, void *w, void *comp, double dt,
              int32_t nsteps, void *stream);
 

@@ -20,16 +20,6 @@ hipError_t launch_rk3_march(const Grid& g, const Phys& P, const Phys* P_dev, int
 
 using namespace mhd;
 
-// One captured step (halo + substep, three times) per starting buffer.
-struct StepGraph {
-    hipGraphExec_t exec = nullptr;
-    const void* f0 = nullptr;
-    const void* f1 = nullptr;
-    const void* w = nullptr;
-    const void* comp = nullptr;
-    double dt = 0.0;
-};
-
 struct mhd_ctx {
     mhd_config cfg;
     mhd_layout lay;
@@ -42,9 +32,6 @@ struct mhd_ctx {
     int device;
     double* red_partials;  // device, REDUCE_BLOCKS doubles, then 1 result
     double* red_host;      // pinned host, 1 double
-    hipStream_t capture_stream;
-    StepGraph graphs[2];   // indexed by the starting buffer
-    bool use_graphs;
 };
 
 namespace {
@@ -83,12 +70,6 @@ int from_hip(hipError_t e)
     if (e == hipSuccess) return MHD_OK;
     if (e == hipErrorOutOfMemory) return MHD_ERR_NOMEM;
     return MHD_ERR_DEVICE;
-}
-
-void drop_graph(StepGraph& gr)
-{
-    if (gr.exec) (void)hipGraphExecDestroy(gr.exec);
-    gr = StepGraph{};
 }
 
 // One launch of the fused kernel over up to six disjoint boxes (the direct
@@ -186,7 +167,9 @@ int substep_args_ok(mhd_ctx* ctx, int32_t s, const void* f_in, const void* f_out
     return MHD_OK;
 }
 
-// Three substeps from buffer `cur`, each after a halo fill of its input.
+// Three substeps from buffer `cur`, each after a halo fill of its input: six
+// launches, which the host issues faster than the smallest grid runs them (a
+// captured graph of them cost 5 us more per step: 16^3 44 against 39 us).
 int step_once(mhd_ctx* ctx, void* const f[2], int cur, void* w, void* comp, double dt,
               hipStream_t st)
 {
@@ -197,35 +180,6 @@ int step_once(mhd_ctx* ctx, void* const f[2], int cur, void* w, void* comp, doub
         if (rc != MHD_OK) return rc;
         cur ^= 1;
     }
-    return MHD_OK;
-}
-
-int ensure_graph(mhd_ctx* ctx, void* const f[2], int cur, void* w, void* comp, double dt)
-{
-    StepGraph& gr = ctx->graphs[cur];
-    if (gr.exec && gr.f0 == f[0] && gr.f1 == f[1] && gr.w == w && gr.comp == comp && gr.dt == dt)
-        return MHD_OK;
-    drop_graph(gr);
-    hipStream_t cs = ctx->capture_stream;
-    hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
-    if (e != hipSuccess) return from_hip(e);
-    int rc = step_once(ctx, f, cur, w, comp, dt, cs);
-    hipGraph_t graph = nullptr;
-    e = hipStreamEndCapture(cs, &graph);
-    if (rc != MHD_OK || e != hipSuccess) {
-        if (graph) (void)hipGraphDestroy(graph);
-        return rc != MHD_OK ? rc : from_hip(e);
-    }
-    hipGraphExec_t exec = nullptr;
-    e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(graph);
-    if (e != hipSuccess) return from_hip(e);
-    gr.exec = exec;
-    gr.f0 = f[0];
-    gr.f1 = f[1];
-    gr.w = w;
-    gr.comp = comp;
-    gr.dt = dt;
     return MHD_OK;
 }
 
@@ -350,14 +304,11 @@ int mhd_init(const mhd_config* cfg, mhd_ctx** out, mhd_layout* layout)
     if (e == hipSuccess) e = hipMalloc(&ctx->phys_dev, sizeof(Phys));
     if (e == hipSuccess) e = hipMemcpy(ctx->phys_dev, &ctx->phys, sizeof(Phys), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipHostMalloc(&ctx->red_host, sizeof(double), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking);
     if (e != hipSuccess) {
         rc = from_hip(e);
         mhd_finalize(ctx);
         return rc;
     }
-    // capture-and-replay pays off where launch latency rivals kernel time
-    ctx->use_graphs = (int64_t)cfg->nx * cfg->ny * cfg->nz <= (int64_t)128 * 128 * 128;
     *layout = L;
     *out = ctx;
     return MHD_OK;
@@ -366,8 +317,6 @@ int mhd_init(const mhd_config* cfg, mhd_ctx** out, mhd_layout* layout)
 void mhd_finalize(mhd_ctx* ctx)
 {
     if (!ctx) return;
-    for (auto& gr : ctx->graphs) drop_graph(gr);
-    if (ctx->capture_stream) (void)hipStreamDestroy(ctx->capture_stream);
     if (ctx->red_partials) (void)hipFree(ctx->red_partials);
     if (ctx->phys_dev) (void)hipFree(ctx->phys_dev);
     if (ctx->ev_ready) (void)hipEventDestroy(ctx->ev_ready);
@@ -401,13 +350,7 @@ int mhd_step(mhd_ctx* ctx, void* const f[2], int32_t* cur, void* w, void* comp, 
     hipStream_t st = (hipStream_t)stream;
     int c = *cur;
     for (int32_t t = 0; t < nsteps; ++t) {
-        if (ctx->use_graphs) {
-            rc = ensure_graph(ctx, f, c, w, comp, dt);
-            if (rc != MHD_OK) return rc;
-            rc = from_hip(hipGraphLaunch(ctx->graphs[c].exec, st));
-        } else {
-            rc = step_once(ctx, f, c, w, comp, dt, st);
-        }
+        rc = step_once(ctx, f, c, w, comp, dt, st);
         if (rc != MHD_OK) return rc;
         c ^= 1;  // three swaps per step
         *cur = c;
