@@ -21,7 +21,8 @@
  *     (output channels padded to 32 with zero rows); tap t covers offsets
  *     (dz, dy, dx) in {-1,0,1}^3 with t = 9(dz+1) + 3(dy+1) + (dx+1).
  *     FP32 master weights are [cout][27][cin].
- *   - Accumulation is FP32 on the MFMA units (v_mfma_f32_32x32x16_bf16).
+ *   - Accumulation is FP32 on the MFMA units (v_mfma_f32_16x16x32_bf16,
+ *     v_mfma_f32_32x32x16_bf16).
  *   - Return values are MHD_OK (0) or MHD_ERR_INVALID (1) / MHD_ERR_DEVICE (3).
  */
 #ifndef MHDNN_H

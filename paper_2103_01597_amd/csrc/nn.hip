@@ -1,22 +1,14 @@
 // Learned-closure kernels for gfx950 (declared in include/mhdnn.h).
 //
 // Periodic 3x3x3 convolutions run as implicit GEMMs on the BF16 matrix
-// cores (v_mfma_f32_32x32x16_bf16, FP32 accumulation).  A block of 512
-// threads owns a slab of 256 cells per plane (full periodic rows) and
-// marches it through a chunk of planes, with a three-plane ring of the slab
-// plus one row on each side in LDS and the next plane prefetched into
-// registers:
-//   * forward / data gradient: M = cells, N = output channels (padded to
-//     32), K = 27 taps x input channels.  An A fragment is 8 consecutive
-//     channels of one shifted cell (one 16-byte LDS read); a B fragment is 8
-//     consecutive input channels of one weight row, held in registers for
-//     the whole march (the LDS then serves only A fragments).  8 input
-//     channels: each wave owns 32 cells and all of K (14 fragments).  32
-//     input channels: the 27 x 2 fragments of all of K would not fit one
-//     lane's registers, so waves 0-3 take input channels 0-15 and waves 4-7
-//     channels 16-31, each over 64 cells (two M tiles); wave w and w+4 then
-//     add their partial sums through LDS, each finishing one tile.
-//   * weight gradient (9 waves): M = output channels, N = input channels (or
+// cores (FP32 accumulation).  A block owns a slab of 256 cells per plane
+// (full periodic rows) and marches it through a chunk of planes, with a ring
+// of planes (the slab plus one row on each side) in LDS and the next plane
+// prefetched into registers:
+//   * forward / data gradient (v_mfma_f32_16x16x32_bf16): M = output
+//     channels, N = cells, K = 32 input channels of one tap, or 4 taps x 8
+//     channels; see k_conv.
+//   * weight gradient (v_mfma_f32_32x32x16_bf16, 9 waves): M = output channels, N = input channels (or
 //     4 taps x 8 channels for 8-channel inputs), K = cells; wave w owns the
 //     taps of x shift w/3 - 1 and z offset w%3 - 1.  Over one full periodic
 //     x-row, sum_x dz(x) x(x + dx) = sum_q dz(q - dx) x(q), so the x shift is
@@ -24,9 +16,10 @@
 //     fragment is 8 consecutive, 16-byte aligned cells of one channel.
 //     Per-block partial sums go to a workspace that a second kernel reduces
 //     in a fixed order (deterministic).
-// MFMA lane layout (32x32x16): lane l holds A row l%32 and B column l%32 at
-// K = 8(l/32)..8(l/32)+7; accumulator r of lane l is D[8(r/4) + 4(l/32) +
-// r%4][l%32].
+// MFMA lane layouts.  16x16x32: lane l holds A row l%16 and B column l%16 at
+// K = 8(l/16)..8(l/16)+7; accumulator i of lane l is D[4(l/16) + i][l%16].
+// 32x32x16: A row l%32 and B column l%32 at K = 8(l/32)..8(l/32)+7;
+// accumulator r is D[8(r/4) + 4(l/32) + r%4][l%32].
 #include <mutex>
 
 #include "mhd_internal.hpp"
@@ -41,7 +34,12 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+// four consecutive channels of one cell, wherever the caller's buffer starts
+// (one access each; the hardware takes unaligned ones)
+typedef unsigned short u16x4 __attribute__((ext_vector_type(4), aligned(2)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -94,14 +92,31 @@ constexpr int NTHR = 256;
 // 2: data gradient (times GELU'(zprev), BF16).
 //
 // A block of CONV_THR threads owns a slab of CONV_CELLS / n full periodic
-// rows (CONV_CELLS cells per plane: 32 per wave for 8 input channels, 64 per
-// wave and half of K for 32) and marches it through a chunk of zc planes.
-// LDS holds a ring of three planes of the slab plus one periodic row on each
-// side (channels last) and, for 32 input channels, the partial-sum hand-over
-// area; the weights stay in registers.  Plane p+2 is fetched into registers
-// while plane p is computed, so each input value is read from memory
-// (1 + 2 RY^-1)(1 + 2 zc^-1) times instead of once per 3 x (rows + 2)
-// neighbourhood of a small tile.
+// rows and marches it through a chunk of zc planes; each of its 8 waves owns
+// 64 of the slab plane's cells (four tiles of 16, whole rows: w % 4) and 16 of
+// the output channels (w / 4).  With 8 output channels waves 4..7 only move
+// planes.  The weights are the A operand and stay in registers for the whole
+// march; the cells are the B operand, so that a lane ends with four
+// consecutive output channels of a cell and stores them in one access.
+//
+// The bound is the instruction stream of a wave (LDS fragment reads, products,
+// the rounding and GELU of the results), not memory (0.2 of the time at the
+// copy rate).  So:
+//   * one fragment read serves the three taps along x: each has an accumulator
+//     of its own over the unshifted cells, and the three are shifted and added
+//     at the plane's end by DPP moves inside the rows of 16 lanes.  That is 9
+//     (3) reads per tile and plane for 32 (8) input channels instead of 27
+//     (14) of a shifted cell each, and no partial sums pass through LDS.
+//   * the ring holds four planes, so one barrier per plane is enough.
+//   * with 32 input channels waves w and w + 4 share a SIMD unit; one finishes
+//     a plane right after its products, the other during the next plane, before
+//     that one's products: one's epilogue then runs beside the other's matrix
+//     instructions.  With 8 input channels the products are too few for that;
+//     each wave's epilogue is interleaved with its own next products instead.
+// 4 fields of 64^3 cells, 8 -> 32, 32 -> 32 and 32 -> 8 channels, forward: 62, 96
+// and 54 us with a read per tap, 32x32x16 products and scalar stores; 52, 74 and 37
+// now (data gradients of the last two: 97 and 58, now 78 and 50).  Without the
+// skew 32 -> 32 takes 81; with it 8 -> 32 takes 62.
 constexpr int CONV_THR = 512;
 constexpr int WG_THR = 576;  // weight gradient: 9 waves, one per (dx, dz) tap triple
 constexpr int CONV_CELLS = 256;  // cells per plane per block
@@ -112,296 +127,238 @@ constexpr int CONV_CELLS = 256;  // cells per plane per block
 template <int CIN>
 constexpr int conv_cp() { return CIN == 32 ? CIN + 8 : CIN; }
 
-template <int CIN>
-constexpr int conv_loads(int n)  // 16-byte vectors each thread moves per plane
+// DPP moves within rows of 16 lanes (one tile of cells): lane x takes lane x -+ 1,
+// the first (last) lane takes the last (first) lane of the tile before (after).
+__device__ __forceinline__ float from_left(float v, float left_tile)
 {
-    return ((CONV_CELLS / n + 2) * n * CIN / 8 + CONV_THR - 1) / CONV_THR;
+    const int edge = __builtin_amdgcn_update_dpp(0, __float_as_int(left_tile), 0x121, 0xf, 0xf, true);
+    return __int_as_float(__builtin_amdgcn_update_dpp(edge, __float_as_int(v), 0x111, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float from_right(float v, float right_tile)
+{
+    const int edge = __builtin_amdgcn_update_dpp(0, __float_as_int(right_tile), 0x12f, 0xf, 0xf, true);
+    return __int_as_float(__builtin_amdgcn_update_dpp(edge, __float_as_int(v), 0x101, 0xf, 0xf, false));
 }
 
-template <int CIN, int MODE>
+template <int CIN, int MODE, int LOGN, int COUT>
 __global__ __launch_bounds__(CONV_THR) void k_conv(const uint16_t* __restrict__ x,
                                                    const uint16_t* __restrict__ w,
                                                    const float* __restrict__ bias,
-                                                   const uint16_t* __restrict__ zprev, int n,
-                                                   int logn, int nch, int zc, int cout,
-                                                   uint16_t* __restrict__ out0,
+                                                   const uint16_t* __restrict__ zprev, int nch,
+                                                   int zc, uint16_t* __restrict__ out0,
                                                    uint16_t* __restrict__ out1,
                                                    float* __restrict__ outf)
 {
     extern __shared__ __align__(16) uint16_t sm[];
-    constexpr int CP = conv_cp<CIN>();
-    const int RY = CONV_CELLS >> logn;       // rows per slab
-    const int slot = (RY + 2) * n * CP;      // elements per ring plane
-    const int nv = (RY + 2) * n * CIN / 8;   // 16-byte vectors per ring plane
-    uint16_t* lx = sm;                       // [3][RY+2][n][CP]
-    // CIN == 32: partial sums handed between wave w and w+4, [8 waves][16][64 lanes]
-    float* red = reinterpret_cast<float*>(sm + 3 * slot);
-    const int slabs = n / RY;
+    constexpr int CP = conv_cp<CIN>(), n = 1 << LOGN;
+    constexpr int RY = CONV_CELLS >> LOGN;        // rows per slab
+    constexpr int SLOT = (RY + 2) * n * CP;       // elements per ring plane
+    constexpr int NV = (RY + 2) * n * CIN / 8;    // 16-byte vectors per ring plane
+    uint16_t* lx = sm;                            // [4][RY+2][n][CP]; CIN 8: and one cell of zeros
+    constexpr int slabs = n / RY;
     const int col_id = blockIdx.x / nch, ch_id = blockIdx.x - col_id * nch;
     const int b = col_id / slabs, y0 = (col_id - b * slabs) * RY;
     const int z0 = ch_id * zc, nz = min(zc, n - z0);
-    const size_t n3 = (size_t)n * n * n;
+    constexpr size_t n3 = (size_t)n * n * n;
     const uint16_t* xb = x + (size_t)b * n3 * CIN;
-    const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63, h = l >> 5, col = l & 31;
+    const int tid = threadIdx.x, l = tid & 63, q16 = l >> 4, c16 = l & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ch0 = 16 * (wv >> 2);               // this wave's output channels
+    const int mbase = 64 * (wv & 3);              // and its cells of the slab plane
 
-    // ---- B fragments (weights, [32][27][CIN] with output channels padded to
-    // 32) for the whole march: lane l holds column l%32, K chunk 8(l/32)
-    constexpr int NB = CIN == 32 ? 27 : 14;
-    // K half of this wave (32 input channels), visibly wave-uniform
-    const int kh = CIN == 32 ? __builtin_amdgcn_readfirstlane(wv >> 2) : 0;
-    bf16x8 bw[NB];
+    // ---- A fragments (weights, [32][27][CIN] with output channels padded to
+    // 32) for the whole march, tap t = 3 p + dxi, p = 3 (dz + 1) + (dy + 1):
+    // lane l holds row l%16.  32 input channels: K chunk 8(l/16) of tap t.  8:
+    // quarter l/16 takes pair p = 4 g + l/16, so that one product spans four.
+    constexpr int NP = CIN == 32 ? 9 : 3;
+    bf16x8 aw[NP][3];
 #pragma unroll
-    for (int u = 0; u < NB; ++u) {
-        if constexpr (CIN == 32) {
-            bw[u] = frag(w + ((size_t)col * 27 + u) * 32 + 16 * kh + 8 * h);
-        } else {  // taps 2u (lanes 0-31) and 2u+1 (lanes 32-63) share one K chunk
-            const int t = 2 * u + h;
-            bw[u] = t < 27 ? frag(w + ((size_t)col * 27 + t) * 8) : bf16x8{};
-        }
-    }
-
-    // ---- plane loads: vector i of ring plane z = rows y0-1 .. y0+RY (periodic)
-    constexpr int NL = conv_loads<CIN>(16) > conv_loads<CIN>(64) ? conv_loads<CIN>(16)
-                                                                    : conv_loads<CIN>(64);
-    u16x8 pre[NL];
-    auto load = [&](int z) {
-        const int zz = (z + n) & (n - 1);
+    for (int g = 0; g < NP; ++g)
 #pragma unroll
-        for (int k = 0; k < NL; ++k) {
-            const int i = tid + k * CONV_THR;
-            if (i < nv) {
-                const int e = i * 8, cell = e / CIN, ch = e - cell * CIN;
-                const int xx = cell & (n - 1), r = cell >> logn;
-                const int yy = (y0 - 1 + r + n) & (n - 1);
-                const size_t src = ((size_t)((zz << logn) + yy) << logn) + xx;
-                pre[k] = *reinterpret_cast<const u16x8*>(xb + src * CIN + ch);
+        for (int dxi = 0; dxi < 3; ++dxi) {
+            const uint16_t* row = w + (size_t)(ch0 + c16) * 27 * CIN;
+            if constexpr (CIN == 32) {
+                aw[g][dxi] = frag(row + (3 * g + dxi) * 32 + 8 * q16);
+            } else {
+                const int p = 4 * g + q16;
+                aw[g][dxi] = p < 9 ? frag(row + (3 * p + dxi) * 8) : bf16x8{};
             }
         }
+
+    // ---- plane loads: vector i of ring plane z = rows y0-1 .. y0+RY (periodic).
+    // Threads past the last vector skip it (MASKED), or move it once more, which
+    // costs registers for the clamped places but leaves the loop without a branch.
+    constexpr int NL = (NV + CONV_THR - 1) / CONV_THR;
+    constexpr bool MASKED = CIN == 32 && NV % CONV_THR != 0;
+    u16x8 pre[NL];
+    unsigned src[NL];  // this lane's vectors within a plane,
+    int dst[NL];       // and in the ring
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        const int i = tid + k * CONV_THR, e = (MASKED ? i : min(i, NV - 1)) * 8;
+        const int cell = e / CIN, ch = e - cell * CIN;
+        const int xx = cell & (n - 1), yy = (y0 - 1 + (cell >> LOGN) + n) & (n - 1);
+        src[k] = (unsigned)(((yy << LOGN) + xx) * CIN + ch);
+        dst[k] = cell * CP + ch;
+    }
+    auto mine = [&](int k) { return !MASKED || tid + k * CONV_THR < NV; };
+    auto load = [&](int z) {
+        const uint16_t* plane = xb + ((size_t)((z + n) & (n - 1)) << (2 * LOGN)) * CIN;
+#pragma unroll
+        for (int k = 0; k < NL; ++k)
+            if (mine(k)) pre[k] = *reinterpret_cast<const u16x8*>(plane + src[k]);
     };
     auto store = [&](int sl) {
 #pragma unroll
-        for (int k = 0; k < NL; ++k) {
-            const int i = tid + k * CONV_THR;
-            if (i < nv) {
-                const int e = i * 8, cell = e / CIN, ch = e - cell * CIN;
-                *reinterpret_cast<u16x8*>(lx + sl * slot + cell * CP + ch) = pre[k];
-            }
-        }
+        for (int k = 0; k < NL; ++k)
+            if (mine(k)) *reinterpret_cast<u16x8*>(lx + sl * SLOT + dst[k]) = pre[k];
     };
+    if (CIN == 8 && tid < 8) lx[4 * SLOT + tid] = 0;
     load(z0 - 1);
     store(0);
     load(z0);
     store(1);
     load(z0 + 1);
 
-    // A-row cells of this lane within the slab plane: one M tile (CIN 8) or two
-    constexpr int NT = CIN == 32 ? 2 : 1;
-    const int mbase = CIN == 32 ? 64 * (wv & 3) : 32 * wv;
-    int rr[NT], xx[NT];
+    const int ch = ch0 + 4 * q16;  // first of this lane's four output channels
+    float bv[4];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) {
-        const int m = mbase + 32 * j + col;
-        rr[j] = m >> logn;
-        xx[j] = m & (n - 1);
-    }
-    // the tile this wave finishes (after the partial-sum hand-over for CIN 32)
-    const int fin = CIN == 32 ? kh : 0;
-    for (int p = 0; p < nz; ++p) {
-        // ring slot q holds plane z0 - 1 + (p' mod 3) for the p' with p' = q (mod 3)
-        store((p + 2) % 3);  // plane z0+p+1 replaces plane z0+p-2
-        __syncthreads();
-        if (p + 1 < nz) load(z0 + p + 2);
-        const int sb[3] = {(p % 3) * (RY + 2), ((p + 1) % 3) * (RY + 2), ((p + 2) % 3) * (RY + 2)};
-        const size_t c0 = (size_t)b * n3 + ((size_t)(z0 + p) << (2 * logn)) + ((size_t)y0 << logn);
-        // data gradient: the layer's pre-activations for this plane's outputs,
-        // fetched now so that their latency overlaps the MFMA loop
-        uint16_t zp[16];
-        if constexpr (MODE == 2) {
-            if (col < cout) {
+    for (int i = 0; i < 4; ++i) bv[i] = MODE != 2 && ch < COUT ? bias[ch + i] : 0.0f;
+    // element of the outputs where the slab's plane z0 + p starts (uniform), and
+    // this lane's channels of its first tile's cell from there
+    auto out_plane = [&](int p) {
+        return ((size_t)b * n3 + ((size_t)(z0 + p) << (2 * LOGN)) + ((size_t)y0 << LOGN)) * COUT;
+    };
+    const unsigned lane_out = (unsigned)((mbase + c16) * COUT + ch);
+    floatx4 res[4];
+    u16x4 zp[4];
+    auto finish = [&](int p) {  // plane z0 + p's results, four channels per lane and tile
+        if (COUT < 32 && ch >= COUT) return;
+        const size_t at = out_plane(p);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int cl = mbase + 32 * fin + 8 * (r >> 2) + 4 * h + (r & 3);
-                    zp[r] = zprev[(c0 + cl) * cout + col];
-                }
-            }
-        }
-
-        floatx16 acc[NT];
+        for (int j = 0; j < 4; ++j) {
+            const unsigned o = lane_out + 16 * j * COUT;
+            u16x4 a, g;
+            floatx4 v;
 #pragma unroll
-        for (int j = 0; j < NT; ++j) acc[j] = floatx16{};
-        if constexpr (CIN == 32) {
-#pragma unroll
-            for (int t = 0; t < 27; ++t) {
-                const int dz = t / 9, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int s = (sb[dz] + rr[j] + dy + 1) * n + ((xx[j] + dx) & (n - 1));
-                    const bf16x8 a = frag(lx + s * CP + 16 * kh + 8 * h);
-                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bw[t], acc[j], 0, 0, 0);
-                }
-            }
-            // Hand the tile the partner finishes to it; the finished tile ends
-            // in acc[0].  Every ring read of this plane is done once all waves
-            // pass the barrier below, so it also orders the next ring store.
-            float* mine = red + wv * 16 * 64 + l;
-            if (kh == 0) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mine[r * 64] = acc[1][r];
-            } else {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mine[r * 64] = acc[0][r];
-            }
-            __syncthreads();
-            const float* theirs = red + (wv ^ 4) * 16 * 64 + l;
-            if (kh == 0) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[0][r] += theirs[r * 64];
-            } else {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] + theirs[r * 64];
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < 14; ++u) {
-                const int t = 2 * u + h;
-                bf16x8 a = {};
-                if (t < 27) {
-                    const int dz = t / 9, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;
-                    const int s = (sb[dz] + rr[0] + dy + 1) * n + ((xx[0] + dx) & (n - 1));
-                    a = frag(lx + s * CP);
-                }
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bw[u], acc[0], 0, 0, 0);
-            }
-        }
-
-        if (col < cout) {
-            const float bv = (MODE == 2) ? 0.0f : bias[col];
-            const floatx16& res = acc[0];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int cl = mbase + 32 * fin + 8 * (r >> 2) + 4 * h + (r & 3);
-                const size_t o = (c0 + cl) * cout + col;
-                const float v = res[r] + bv;
+            for (int i = 0; i < 4; ++i) {
+                v[i] = res[j][i] + bv[i];
                 if constexpr (MODE == 0) {
-                    out0[o] = f2bf(v);
-                    out1[o] = f2bf(gelu(v));
-                } else if constexpr (MODE == 1) {
-                    outf[o] = v;
-                } else {
-                    out0[o] = f2bf(v * gelu_grad(bf2f(zp[r])));
+                    a[i] = f2bf(v[i]);
+                    g[i] = f2bf(gelu(v[i]));
+                } else if constexpr (MODE == 2) {
+                    a[i] = f2bf(v[i] * gelu_grad(bf2f(zp[j][i])));
                 }
             }
+            if constexpr (MODE == 1)
+                *reinterpret_cast<f32x4u*>(outf + at + o) = v;
+            else
+                *reinterpret_cast<u16x4*>(out0 + at + o) = a;
+            if constexpr (MODE == 0) *reinterpret_cast<u16x4*>(out1 + at + o) = g;
         }
-        // CIN 8: every read of plane z0+p-1 is done before it is replaced.
-        // CIN 32: the hand-over barrier above already ordered them, and the
-        // next plane's partial sums are written only after its first barrier.
-        if constexpr (CIN != 32) __syncthreads();
-    }
-}
-
-// Output layer with 8 output channels (32 input channels): the same slab
-// march as k_conv, on the 16 x 16 x 32 BF16 MFMA, whose N of 16 pads the
-// 8 output channels half as much as the 32 x 32 x 16 shape's N of 32 (and
-// whose K of 32 takes all input channels of a tap at once, so no wave pair
-// splits K).  Each wave owns 32 cells (two M tiles of 16).  Lane layout:
-// A[row l%16][k 8(l/16)..+7], B[k 8(l/16)..+7][col l%16], D[row 4(l/16)+i][col l%16].
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-__global__ __launch_bounds__(CONV_THR) void k_conv_out8(const uint16_t* __restrict__ x,
-                                                       const uint16_t* __restrict__ w,
-                                                       const float* __restrict__ bias, int n,
-                                                       int logn, int nch, int zc,
-                                                       float* __restrict__ outf)
-{
-    extern __shared__ __align__(16) uint16_t sm[];
-    constexpr int CIN = 32, COUT = 8;
-    constexpr int CP = conv_cp<CIN>();
-    const int RY = CONV_CELLS >> logn;
-    const int slot = (RY + 2) * n * CP;
-    const int nv = (RY + 2) * n * CIN / 8;
-    uint16_t* lx = sm;  // [3][RY+2][n][CP]
-    const int slabs = n / RY;
-    const int col_id = blockIdx.x / nch, ch_id = blockIdx.x - col_id * nch;
-    const int b = col_id / slabs, y0 = (col_id - b * slabs) * RY;
-    const int z0 = ch_id * zc, nz = min(zc, n - z0);
-    const size_t n3 = (size_t)n * n * n;
-    const uint16_t* xb = x + (size_t)b * n3 * CIN;
-    const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63, q16 = l >> 4, c16 = l & 15;
-
-    // B fragments for the whole march: column c16 (output channel; rows
-    // o >= 8 of w_pad are zero), K chunk 8 q16 of every tap
-    bf16x8 bw[27];
+    };
+    int rbase[4];  // tile j's cell of this lane in the ring plane, row dy = -1
 #pragma unroll
-    for (int t = 0; t < 27; ++t) bw[t] = frag(w + ((size_t)c16 * 27 + t) * 32 + 8 * q16);
-
-    constexpr int NL = conv_loads<CIN>(16) > conv_loads<CIN>(64) ? conv_loads<CIN>(16)
-                                                                    : conv_loads<CIN>(64);
-    u16x8 pre[NL];
-    auto load = [&](int z) {
-        const int zz = (z + n) & (n - 1);
+    for (int j = 0; j < 4; ++j) rbase[j] = (mbase + 16 * j + c16) * CP + (CIN == 32 ? 8 * q16 : 0);
+    // the pre-activations of plane z0 + p's outputs (data gradient)
+    auto load_zp = [&](int p) {
+        if constexpr (MODE == 2) {
+            if (COUT < 32 && ch >= COUT) return;
 #pragma unroll
-        for (int k = 0; k < NL; ++k) {
-            const int i = tid + k * CONV_THR;
-            if (i < nv) {
-                const int e = i * 8, cell = e / CIN, ch = e - cell * CIN;
-                const int xx = cell & (n - 1), r = cell >> logn;
-                const int yy = (y0 - 1 + r + n) & (n - 1);
-                const size_t src = ((size_t)((zz << logn) + yy) << logn) + xx;
-                pre[k] = *reinterpret_cast<const u16x8*>(xb + src * CIN + ch);
+            for (int j = 0; j < 4; ++j)
+                zp[j] = *reinterpret_cast<const u16x4*>(zprev + out_plane(p) + (lane_out + 16 * j * COUT));
+        }
+    };
+    auto products = [&](int p) {  // plane z0 + p
+        // ring slot q holds the plane z0 - 1 + p' with p' = q (mod 4)
+        floatx4 acc[3][4];  // [dx + 1][tile]
+#pragma unroll
+        for (int dxi = 0; dxi < 3; ++dxi)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[dxi][j] = floatx4{};
+        const int sb[3] = {(p & 3) * SLOT, ((p + 1) & 3) * SLOT, ((p + 2) & 3) * SLOT};
+#pragma unroll
+        for (int g = 0; g < NP; ++g) {
+            int off;  // ring offset of the fragments' (dz, dy) row relative to the cell
+            bool pad = false;  // past the ninth pair: zeros (not a cell, which need not be finite)
+            if constexpr (CIN == 32) {
+                off = sb[g / 3] + (g % 3) * n * CP;
+            } else {
+                const int pr = min(4 * g + q16, 8), dz = pr / 3, dy = pr - 3 * dz;
+                pad = 4 * g + q16 > 8;
+                off = (dz == 0 ? sb[0] : dz == 1 ? sb[1] : sb[2]) + dy * n * CP;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bf16x8 v = frag(lx + (pad ? 4 * SLOT : off + rbase[j]));
+#pragma unroll
+                for (int dxi = 0; dxi < 3; ++dxi)
+                    acc[dxi][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aw[g][dxi], v, acc[dxi][j], 0, 0, 0);
+            }
+        }
+        // y(x) = D_-1(x - 1) + D_0(x) + D_+1(x + 1) along the periodic row, whose
+        // n / 16 tiles are consecutive ones of this wave
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            constexpr int TPR = n / 16;  // tiles per row
+            const int jl = j / TPR * TPR + (j + TPR - 1) % TPR, jr = j / TPR * TPR + (j + 1) % TPR;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                res[j][i] = acc[1][j][i] + from_left(acc[0][j][i], acc[0][jl][i]) +
+                            from_right(acc[2][j][i], acc[2][jr][i]);
+        }
+    };
+    // the instruction order of an epilogue and the products after it: a group's
+    // fragments one group ahead, VPP vector instructions beside each product
+    auto interleave = [&]() {
+        constexpr int VPP = MODE == 1 ? 1 : 11;
+        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+        for (int g = 0; g < NP; ++g) {
+            if (g + 1 < NP) __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+            for (int i = 0; i < 12; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, VPP, 0);
             }
         }
     };
-    auto store = [&](int sl) {
-#pragma unroll
-        for (int k = 0; k < NL; ++k) {
-            const int i = tid + k * CONV_THR;
-            if (i < nv) {
-                const int e = i * 8, cell = e / CIN, ch = e - cell * CIN;
-                *reinterpret_cast<u16x8*>(lx + sl * slot + cell * CP + ch) = pre[k];
-            }
-        }
-    };
-    load(z0 - 1);
-    store(0);
-    load(z0);
-    store(1);
-    load(z0 + 1);
-
-    int rr[2], xx[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int m = 32 * wv + 16 * j + c16;
-        rr[j] = m >> logn;
-        xx[j] = m & (n - 1);
-    }
-    const float bv = c16 < COUT ? bias[c16] : 0.0f;
-    for (int p = 0; p < nz; ++p) {
-        store((p + 2) % 3);  // plane z0+p+1 replaces plane z0+p-2
+    // The plane after next is fetched and the next one put into the ring at each
+    // plane's start; with four slots one barrier per plane is enough (a wave that
+    // runs ahead overwrites the plane before the three that others still read).
+    // Each plane's loads are issued before the stores of the plane finished
+    // beside it, and no branch lies between (the last plane is fetched again
+    // instead): the wait for the loads then counts past exactly those stores.
+    // With a branch the compiler waits for all of them, on every plane.
+    auto turn = [&](int p) {
+        store((p + 2) & 3);  // plane z0+p+1
         __syncthreads();
-        if (p + 1 < nz) load(z0 + p + 2);
-        const int sb[3] = {(p % 3) * (RY + 2), ((p + 1) % 3) * (RY + 2), ((p + 2) % 3) * (RY + 2)};
-        const size_t c0 = (size_t)b * n3 + ((size_t)(z0 + p) << (2 * logn)) + ((size_t)y0 << logn);
-        floatx4 acc[2] = {floatx4{}, floatx4{}};
-#pragma unroll
-        for (int t = 0; t < 27; ++t) {
-            const int dz = t / 9, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int s = (sb[dz] + rr[j] + dy + 1) * n + ((xx[j] + dx) & (n - 1));
-                const bf16x8 a = frag(lx + s * CP + 8 * q16);
-                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bw[t], acc[j], 0, 0, 0);
-            }
+        load(z0 + min(p + 2, nz));
+    };
+    turn(0);
+    if (ch0 >= COUT) {  // no output channels: this wave only moves planes
+        for (int p = 1; p < nz; ++p) turn(p);
+    } else if (CIN == 32 && wv < 4) {
+        load_zp(0);
+        products(0);
+        finish(0);
+        for (int p = 1; p < nz; ++p) {
+            turn(p);
+            load_zp(p);
+            products(p);
+            finish(p);
         }
-        if (c16 < COUT) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int cl = 32 * wv + 16 * j + 4 * q16 + i;
-                    outf[(c0 + cl) * COUT + c16] = acc[j][i] + bv;
-                }
+    } else {
+        products(0);
+        for (int p = 1; p < nz; ++p) {
+            load_zp(p - 1);
+            turn(p);
+            finish(p - 1);
+            products(p);
+            if constexpr (CIN == 8) interleave();
         }
-        __syncthreads();  // every read of plane z0+p-1 is done before it is replaced
+        load_zp(nz - 1);
+        finish(nz - 1);
     }
 }
 
@@ -911,9 +868,24 @@ void conv_chunks(int n, int batch, int& columns, int& nch, int& zc)
 
 size_t conv_lds(int cin, int n)
 {
-    const int cp = cin == 32 ? conv_cp<32>() : conv_cp<8>();
-    const size_t ring = 2 * (3 * (CONV_CELLS / n + 2) * n * cp);
-    return ring + (cin == 32 ? sizeof(float) * 8 * 16 * 64 : 0);  // + partial-sum hand-over
+    return 2 * (4 * (CONV_CELLS / n + 2) * n * (cin == 32 ? conv_cp<32>() : conv_cp<8>()) + 8);
+}
+
+template <int CIN, int MODE, int LOGN, int COUT>
+hipError_t launch_conv_n(const uint16_t* x, const uint16_t* w, const float* bias,
+                         const uint16_t* zp, int batch, uint16_t* o0, uint16_t* o1,
+                         float* of, hipStream_t st)
+{
+    // once per instantiation (thread-safe static initialisation)
+    static const hipError_t attr =
+        hipFuncSetAttribute((const void*)k_conv<CIN, MODE, LOGN, COUT>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)conv_lds(CIN, 1 << LOGN));
+    if (attr != hipSuccess) return attr;
+    int columns, nch, zc;
+    conv_chunks(1 << LOGN, batch, columns, nch, zc);
+    hipLaunchKernelGGL((k_conv<CIN, MODE, LOGN, COUT>), dim3(columns * nch), dim3(CONV_THR),
+                       conv_lds(CIN, 1 << LOGN), st, x, w, bias, zp, nch, zc, o0, o1, of);
+    return hipGetLastError();
 }
 
 template <int CIN, int MODE>
@@ -921,31 +893,15 @@ hipError_t launch_conv(const uint16_t* x, const uint16_t* w, const float* bias, 
                        int n, int batch, int cout, uint16_t* o0, uint16_t* o1, float* of,
                        hipStream_t st)
 {
-    // once per instantiation (thread-safe static initialisation)
-    static const hipError_t attr = hipFuncSetAttribute(
-        (const void*)k_conv<CIN, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize,
-        (int)(conv_lds(CIN, 16) > conv_lds(CIN, 64) ? conv_lds(CIN, 16) : conv_lds(CIN, 64)));
-    if (attr != hipSuccess) return attr;
-    int columns, nch, zc;
-    conv_chunks(n, batch, columns, nch, zc);
-    hipLaunchKernelGGL((k_conv<CIN, MODE>), dim3(columns * nch), dim3(CONV_THR),
-                       conv_lds(CIN, n), st, x, w, bias, zp, n, ilog2(n), nch, zc, cout, o0, o1,
-                       of);
-    return hipGetLastError();
-}
-
-hipError_t launch_conv_out8(const uint16_t* x, const uint16_t* w, const float* bias, int n,
-                            int batch, float* of, hipStream_t st)
-{
-    static const hipError_t attr = hipFuncSetAttribute(
-        (const void*)k_conv_out8, hipFuncAttributeMaxDynamicSharedMemorySize,
-        (int)(conv_lds(32, 16) > conv_lds(32, 64) ? conv_lds(32, 16) : conv_lds(32, 64)));
-    if (attr != hipSuccess) return attr;
-    int columns, nch, zc;
-    conv_chunks(n, batch, columns, nch, zc);
-    hipLaunchKernelGGL(k_conv_out8, dim3(columns * nch), dim3(CONV_THR), conv_lds(32, n), st, x,
-                       w, bias, n, ilog2(n), nch, zc, of);
-    return hipGetLastError();
+#define MHDNN_LAUNCH(LOGN)                                                                     \
+    (cout == 32 ? launch_conv_n<CIN, MODE, LOGN, 32>(x, w, bias, zp, batch, o0, o1, of, st)     \
+                : launch_conv_n<CIN, MODE, LOGN, 8>(x, w, bias, zp, batch, o0, o1, of, st))
+    switch (n) {
+    case 16: return MHDNN_LAUNCH(4);
+    case 32: return MHDNN_LAUNCH(5);
+    default: return MHDNN_LAUNCH(6);
+    }
+#undef MHDNN_LAUNCH
 }
 
 template <int CIN, int COUT>
@@ -1058,8 +1014,6 @@ int mhdnn_conv3d_fwd(const uint16_t* x, const uint16_t* w_pad, const float* bias
                                            nullptr, st)
                       : launch_conv<8, 0>(x, w_pad, bias, nullptr, n, batch, cout, z_bf16, a_bf16,
                                           nullptr, st);
-    else if (cin == 32 && cout == 8)
-        e = launch_conv_out8(x, w_pad, bias, n, batch, y_f32, st);
     else
         e = cin == 32 ? launch_conv<32, 1>(x, w_pad, bias, nullptr, n, batch, cout, nullptr,
                                            nullptr, y_f32, st)
