@@ -8,13 +8,10 @@
 //   * forward / data gradient (v_mfma_f32_16x16x32_bf16): M = output
 //     channels, N = cells, K = 32 input channels of one tap, or 4 taps x 8
 //     channels; see k_conv.
-//   * weight gradient (v_mfma_f32_32x32x16_bf16, 9 waves): M = output channels, N = input channels (or
-//     4 taps x 8 channels for 8-channel inputs), K = cells; wave w owns the
-//     taps of x shift w/3 - 1 and z offset w%3 - 1.  Over one full periodic
-//     x-row, sum_x dz(x) x(x + dx) = sum_q dz(q - dx) x(q), so the x shift is
-//     moved onto three pre-shifted LDS copies of the dz plane and every
-//     fragment is 8 consecutive, 16-byte aligned cells of one channel.
-//     Per-block partial sums go to a workspace that a second kernel reduces
+//   * weight gradient (v_mfma_f32_32x32x16_bf16, 9 waves): M = output
+//     channels, N = input channels (or 4 taps x 8 channels for 8-channel
+//     inputs), K = cells; wave w owns the taps of x shift w/3 - 1 and z
+//     offset w%3 - 1; see k_wgrad.  Per-block partial sums go to a workspace that a second kernel reduces
 //     in a fixed order (deterministic).
 // MFMA lane layouts.  16x16x32: lane l holds A row l%16 and B column l%16 at
 // K = 8(l/16)..8(l/16)+7; accumulator i of lane l is D[4(l/16) + i][l%16].
@@ -367,103 +364,121 @@ __global__ __launch_bounds__(CONV_THR) void k_conv(const uint16_t* __restrict__ 
 // (and db[o] = sum dz[cell][o]) on the same slabs and z chunks as k_conv.
 // M = output channels, N = input channels (or 4 (dz, dy) taps x 8 channels
 // for 8-channel inputs), K = cells.  Over one full periodic x-row,
-// sum_x dz(x) x(x + dx) = sum_q dz(q - dx) x(q), so the x shift is moved onto
-// three pre-shifted LDS copies of the dz plane and every fragment is 8
-// consecutive, 16-byte aligned cells of one channel: x is kept channel-major
-// in a three-plane ring, dz channel-major for the current plane.  Each block
+// sum_x dz(x) x(x + dx) = sum_q dz(q - dx) x(q): the x shift is taken by the
+// dz operand, so that three x rows share its fragment.  Each block
 // accumulates its chunk in registers and writes one partial sum per weight;
 // k_wgrad_reduce adds the partials in a fixed order (deterministic).
-template <int CIN, int COUT>
+//
+// x is kept in a ring of four planes and dz in two alternating ones, both
+// channels last as they come from memory, and a fragment (8 cells of one
+// channel per lane) is two transposing reads: of each 16 lanes lane j names
+// 4 channels of cell j/4, and lane i receives channel i of the 4 cells.  Each
+// lane names its own cell, so the shift and its periodic wrap are part of the
+// address.  The bound is the matrix cores (the 9 waves leave one SIMD unit
+// with three) and the reads beside them.  With transposed planes, written by
+// 2-byte LDS stores with three shifted copies of dz, those stores were: 4 x
+// 64^3 cells, 8 -> 32, 32 -> 32 and 32 -> 8 channels took 74, 100 and 59 us;
+// 41, 69 and 36 now.
+//
+// Bank layout: 4 consecutive cells' 32 bytes must lie in different banks.  32
+// channels: the two halves of a cell's 64 bytes are exchanged in every other
+// pair of cells.  8 channels: rows and planes are padded by 64 bytes, so that
+// the two taps that 16 lanes read lie 64 bytes apart modulo the 128 read at a
+// time.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ bf16x8 frag_cells(const uint16_t* c0, const uint16_t* c4)
+{
+    typedef __attribute__((address_space(3))) s16x4* lds_ptr;
+    union {
+        s16x4 h[2];
+        bf16x8 v;
+    } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)c0);
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)c4);
+    return u.v;
+}
+
+// Offset of channels c, c+1, .. of cell x within an LDS row of C channels
+template <int C>
+__device__ __forceinline__ int in_row(int x, int c)
+{
+    return x * C + (C == 32 ? c ^ ((x & 2) << 3) : c);
+}
+// LDS elements of a row and of a ring plane of x
+template <int CIN>
+constexpr int wg_row(int n) { return n * CIN + (CIN == 8 ? 32 : 0); }
+template <int CIN>
+constexpr int wg_slot(int n) { return (CONV_CELLS / n + 2) * wg_row<CIN>(n) + (CIN == 8 ? 32 : 0); }
+
+template <int CIN, int COUT, int LOGN>
 __global__ __launch_bounds__(WG_THR) void k_wgrad(const uint16_t* __restrict__ x,
-                                                    const uint16_t* __restrict__ dz, int n,
-                                                    int logn, int nch, int zc,
-                                                    float* __restrict__ ws,
+                                                    const uint16_t* __restrict__ dz, int nch,
+                                                    int zc, float* __restrict__ ws,
                                                     float* __restrict__ wsb)
 {
     extern __shared__ __align__(16) uint16_t sm[];
-    const int RY = CONV_CELLS >> logn;
-    const int xplane = (RY + 2) * n;            // cells of one ring plane
-    // channel rows padded by 16 bytes: fragment reads of consecutive lanes
-    // (consecutive channels) start an odd number of 16-byte units apart
-    const int PS = xplane + 8;
-    constexpr int DS = CONV_CELLS + 8;
-    uint16_t* xs = sm;                          // [CIN][3][PS]: rows [RY+2][n]
-    uint16_t* ds = sm + CIN * 3 * PS;           // [3 shifts][32][DS]: rows [RY][n]
-    float* bsum = reinterpret_cast<float*>(ds + 3 * 32 * DS);  // [WG_THR][8]
-    const int slabs = n / RY;
+    constexpr int n = 1 << LOGN, RY = CONV_CELLS >> LOGN;
+    constexpr int ROW = wg_row<CIN>(n), SLOT = wg_slot<CIN>(n), DPLANE = CONV_CELLS * COUT;
+    uint16_t* xs = sm;             // [4 planes][RY + 2][n][CIN]
+    uint16_t* ds = sm + 4 * SLOT;  // [2 planes][RY][n][COUT]
+    float* bsum = reinterpret_cast<float*>(ds + 2 * DPLANE);  // [WG_THR][8]
+    constexpr int slabs = n / RY;
     const int col_id = blockIdx.x / nch, ch_id = blockIdx.x - col_id * nch;
     const int b = col_id / slabs, y0 = (col_id - b * slabs) * RY;
     const int z0 = ch_id * zc, nz = min(zc, n - z0);
-    const size_t n3 = (size_t)n * n * n;
+    constexpr size_t n3 = (size_t)n * n * n;
     const uint16_t* xb = x + (size_t)b * n3 * CIN;
-    const uint16_t* db = dz + (size_t)b * n3 * COUT;
-    const int tid = threadIdx.x, wv = tid >> 6, l = tid & 63, h = l >> 5, col = l & 31;
-
-    // rows o >= COUT of the dz copies stay zero
-    if constexpr (COUT < 32)
-        for (int i = tid; i < 3 * (32 - COUT) * DS; i += WG_THR) {
-            const int sh = i / ((32 - COUT) * DS), rem = i - sh * (32 - COUT) * DS;
-            ds[(sh * 32 + COUT) * DS + rem] = 0;
-        }
+    const uint16_t* db = dz + (size_t)b * n3 * COUT + ((size_t)y0 << LOGN) * COUT;
+    const int tid = threadIdx.x, l = tid & 63, h = l >> 5, col = l & 31;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // ---- plane loads (16-byte vectors of 8 channels of one cell)
-    constexpr int NVX16 = (CONV_CELLS / 16 + 2) * 16 * CIN / 8, NVX64 = (CONV_CELLS / 64 + 2) * 64 * CIN / 8;
-    constexpr int NLX = ((NVX16 > NVX64 ? NVX16 : NVX64) + WG_THR - 1) / WG_THR;
+    constexpr int NVX = (RY + 2) * n * CIN / 8, NLX = (NVX + WG_THR - 1) / WG_THR;
     constexpr int NVD = CONV_CELLS * COUT / 8, NLD = (NVD + WG_THR - 1) / WG_THR;
-    const int nvx = xplane * CIN / 8;
     u16x8 px[NLX], pd[NLD];
     auto load_x = [&](int z) {
-        const int zz = (z + n) & (n - 1);
+        const uint16_t* plane = xb + ((size_t)((z + n) & (n - 1)) << (2 * LOGN)) * CIN;
 #pragma unroll
         for (int k = 0; k < NLX; ++k) {
             const int i = tid + k * WG_THR;
-            if (i < nvx) {
+            if (i < NVX) {
                 const int cell = i / (CIN / 8), cg = (i - cell * (CIN / 8)) * 8;
-                const int xx = cell & (n - 1), r = cell >> logn;
-                const int yy = (y0 - 1 + r + n) & (n - 1);
-                const size_t src = ((size_t)((zz << logn) + yy) << logn) + xx;
-                px[k] = *reinterpret_cast<const u16x8*>(xb + src * CIN + cg);
+                const int yy = (y0 - 1 + (cell >> LOGN) + n) & (n - 1);
+                px[k] = *reinterpret_cast<const u16x8*>(
+                    plane + (((yy << LOGN) + (cell & (n - 1))) * CIN + cg));
             }
         }
     };
-    auto store_x = [&](int sl) {  // transposed to channel-major
+    auto store_x = [&](int sl) {
 #pragma unroll
         for (int k = 0; k < NLX; ++k) {
             const int i = tid + k * WG_THR;
-            if (i < nvx) {
+            if (i < NVX) {
                 const int cell = i / (CIN / 8), cg = (i - cell * (CIN / 8)) * 8;
-#pragma unroll
-                for (int q = 0; q < 8; ++q) xs[((cg + q) * 3 + sl) * PS + cell] = px[k][q];
+                *reinterpret_cast<u16x8*>(xs + sl * SLOT + (cell >> LOGN) * ROW +
+                                          in_row<CIN>(cell & (n - 1), cg)) = px[k];
             }
         }
     };
     auto load_dz = [&](int z) {
+        const uint16_t* plane = db + ((size_t)z << (2 * LOGN)) * COUT;
 #pragma unroll
         for (int k = 0; k < NLD; ++k) {
             const int i = tid + k * WG_THR;
-            if (i < NVD) {
-                const int cell = i / (COUT / 8), og = (i - cell * (COUT / 8)) * 8;
-                const size_t src = ((size_t)z << (2 * logn)) + ((size_t)y0 << logn) + cell;
-                pd[k] = *reinterpret_cast<const u16x8*>(db + src * COUT + og);
-            }
+            if (i < NVD) pd[k] = *reinterpret_cast<const u16x8*>(plane + i * 8);
         }
     };
     float bacc[8] = {};  // bias partials of this thread's 8 output channels
-    auto store_dz = [&]() {  // transposed, in three copies shifted along x
+    auto store_dz = [&](int sl) {
 #pragma unroll
         for (int k = 0; k < NLD; ++k) {
             const int i = tid + k * WG_THR;
             if (i < NVD) {
                 const int cell = i / (COUT / 8), og = (i - cell * (COUT / 8)) * 8;
-                const int xx = cell & (n - 1), rr = cell >> logn;
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const uint16_t v = pd[k][q];
-                    bacc[q] += bf2f(v);
-#pragma unroll
-                    for (int sh = 0; sh < 3; ++sh)
-                        ds[(sh * 32 + og + q) * DS + rr * n + ((xx + sh - 1) & (n - 1))] = v;
-                }
+                for (int q = 0; q < 8; ++q) bacc[q] += bf2f(pd[k][q]);
+                *reinterpret_cast<u16x8*>(ds + sl * DPLANE + in_row<COUT>(cell, og)) = pd[k];
             }
         }
     };
@@ -473,7 +488,7 @@ __global__ __launch_bounds__(WG_THR) void k_wgrad(const uint16_t* __restrict__ x
     // the three share each dz fragment; CIN 8: tap group g = wv (g = 3*dxi +
     // gi, gi selects 4 of the 9 (dz, dy) pairs).  CIN 32 with 8 output
     // channels: the 32 rows of the one set are (dx shift, o) pairs, rows
-    // 8 (dx + 1) + o, the last 8 rows zero, for the taps with dz = wv%3 - 1
+    // 8 (dx + 1) + o, the last 8 rows unused, for the taps with dz = wv%3 - 1
     // and dy = wv/3 - 1 (three times fewer products than three sets of 8
     // channels padded to 32).
     constexpr bool PACK_DX = CIN == 32 && COUT == 8;
@@ -482,6 +497,23 @@ __global__ __launch_bounds__(WG_THR) void k_wgrad(const uint16_t* __restrict__ x
 #pragma unroll
     for (int i = 0; i < NSET; ++i) acc[i] = floatx16{};
 
+    // ---- what this lane names for a chunk of 16 cells from q0 in a row, in
+    // its two reads (t = 0, 1): cell q0 + 8h + 4t + jc, channels (or tap and
+    // channels) j4 .. j4 + 3 of the operand's 32
+    const int jc = (l & 15) >> 2, j4 = 16 * ((l >> 4) & 1) + 4 * (l & 3);
+    // dz at q - dx: only the first cell of a row (dx = 1) and the last one
+    // (dx = -1) wrap, in the row's first and last chunk.  Output channels past
+    // COUT repeat others and are not written.
+    const int s = PACK_DX ? min(j4 >> 3, 2) : wv / 3;  // dx + 1
+    const int o4 = COUT == 8 ? j4 & 7 : j4, e0 = 8 * h + jc + 1 - s, e1 = e0 + 4;
+    // (e0 + 16: the pattern of in_row repeats every 4 cells)
+    const int d0 = in_row<COUT>(e0 + 16, o4) - 16 * COUT, d0_first = d0 + (e0 < 0 ? n * COUT : 0);
+    const int d1 = in_row<COUT>(e1, o4), d1_last = d1 - (e1 > 15 ? n * COUT : 0);
+    // x: the ring plane dz + 1 and the offset in it
+    const int pr = min(4 * (wv % 3) + (j4 >> 3), 8);  // CIN 8: (dz, dy) pair, the last repeated
+    const int xz = CIN == 8 ? pr / 3 : wv % 3, xy = CIN == 8 ? pr % 3 : PACK_DX ? wv / 3 : 0;
+    const int xo = xy * ROW + in_row<CIN>(8 * h + jc, CIN == 8 ? j4 & 7 : j4);
+
     load_x(z0 - 1);
     store_x(0);
     load_x(z0);
@@ -489,44 +521,27 @@ __global__ __launch_bounds__(WG_THR) void k_wgrad(const uint16_t* __restrict__ x
     load_x(z0 + 1);
     load_dz(z0);
     for (int p = 0; p < nz; ++p) {
-        store_x((p + 2) % 3);  // plane z0+p+1 replaces plane z0+p-2
-        store_dz();            // plane z0+p
-        __syncthreads();
+        store_x((p + 2) & 3);  // plane z0+p+1 replaces plane z0+p-3
+        store_dz(p & 1);       // plane z0+p
+        __syncthreads();       // (all waves are past the products of plane z0+p-1)
         if (p + 1 < nz) {
             load_x(z0 + p + 2);
             load_dz(z0 + p + 1);
         }
-        const int sb[3] = {p % 3, (p + 1) % 3, (p + 2) % 3};  // ring slot of plane dz = -1, 0, 1
-        const int dxs = wv / 3;  // shift copy s = dx + 1 (both channel counts)
-        // PACK_DX: lane row col = 8 (dx + 1) + o; the rows past the three
-        // shifts read a zero row (o + 8 >= COUT) of the first copy
-        const int arow = PACK_DX ? (col < 24 ? (col >> 3) * 32 + (col & 7) : 8 + (col & 7))
-                                 : dxs * 32 + col;
-#pragma unroll 4
-        for (int kc = 0; kc < CONV_CELLS / 16; ++kc) {
-            const int cell = kc * 16 + 8 * h;
-            const int rr = cell >> logn, xq = cell & (n - 1);
-            const bf16x8 a = frag(ds + arow * DS + rr * n + xq);
-            if constexpr (PACK_DX) {
-                const uint16_t* xrow = xs + (col * 3 + sb[wv % 3]) * PS + (rr + wv / 3) * n + xq;
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, frag(xrow), acc[0], 0, 0, 0);
-            } else if constexpr (CIN == 32) {
-                const uint16_t* xrow = xs + (col * 3 + sb[wv % 3]) * PS + rr * n + xq;
+        const uint16_t* xl = xs + ((p + xz) & 3) * SLOT + xo;
+        const uint16_t* dl = ds + (p & 1) * DPLANE;
 #pragma unroll
-                for (int si = 0; si < 3; ++si)  // dy = si - 1
-                    acc[si] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, frag(xrow + si * n),
-                                                                       acc[si], 0, 0, 0);
-            } else {
-                const int tg = col >> 3, c = col & 7, pr = 4 * (wv % 3) + tg;
-                bf16x8 bb = {};
-                if (pr < 9) {
-                    const int dzz = pr / 3 - 1, dyy = pr % 3 - 1;
-                    bb = frag(xs + (c * 3 + sb[dzz + 1]) * PS + (rr + dyy + 1) * n + xq);
-                }
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bb, acc[0], 0, 0, 0);
-            }
+        for (int kc = 0; kc < CONV_CELLS / 16; ++kc) {
+            const int rr = kc * 16 >> LOGN, q0 = kc * 16 & (n - 1);
+            const uint16_t* dk = dl + kc * 16 * COUT;
+            const bf16x8 a = frag_cells(dk + (q0 == 0 ? d0_first : d0),
+                                        dk + (q0 + 16 == n ? d1_last : d1));
+            const uint16_t* xk = xl + rr * ROW + q0 * CIN;
+#pragma unroll
+            for (int si = 0; si < NSET; ++si)  // dy = si - 1
+                acc[si] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    a, frag_cells(xk + si * ROW, xk + si * ROW + 4 * CIN), acc[si], 0, 0, 0);
         }
-        __syncthreads();  // reads of plane z0+p-1 and of the dz plane are done
     }
 
     // ---- this block's partial sums: ws[block][t][o][c], wsb[block][o]
@@ -536,6 +551,7 @@ __global__ __launch_bounds__(WG_THR) void k_wgrad(const uint16_t* __restrict__ x
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int o = 8 * (r >> 2) + 4 * h + (r & 3);
+            if (!PACK_DX && o >= COUT) continue;
             int t, c, oo = o;
             if constexpr (PACK_DX) {
                 if (o >= 24) continue;
@@ -849,9 +865,9 @@ bool conv_n_ok(int n) { return n == 16 || n == 32 || n == 64; }
 
 int status(hipError_t e) { return e == hipSuccess ? MHD_OK : MHD_ERR_DEVICE; }
 
-size_t wgrad_lds(int cin, int n)
+size_t wgrad_lds(int cin, int cout, int n)
 {
-    return 2 * (cin * 3 * ((CONV_CELLS / n + 2) * n + 8) + 3 * 32 * (CONV_CELLS + 8)) +
+    return 2 * (4 * (cin == 32 ? wg_slot<32>(n) : wg_slot<8>(n)) + 2 * CONV_CELLS * cout) +
            4 * WG_THR * 8;
 }
 
@@ -904,21 +920,30 @@ hipError_t launch_conv(const uint16_t* x, const uint16_t* w, const float* bias, 
 #undef MHDNN_LAUNCH
 }
 
+template <int CIN, int COUT, int LOGN>
+hipError_t launch_wgrad_n(const uint16_t* x, const uint16_t* dz, int blocks, int nch, int zc,
+                          float* ws, float* wsb, hipStream_t st)
+{
+    static const hipError_t attr = hipFuncSetAttribute(
+        (const void*)k_wgrad<CIN, COUT, LOGN>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        (int)wgrad_lds(CIN, COUT, 1 << LOGN));
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL((k_wgrad<CIN, COUT, LOGN>), dim3(blocks), dim3(WG_THR),
+                       wgrad_lds(CIN, COUT, 1 << LOGN), st, x, dz, nch, zc, ws, wsb);
+    return hipGetLastError();
+}
+
 template <int CIN, int COUT>
 hipError_t launch_wgrad(const uint16_t* x, const uint16_t* dz, int n, int batch, float* ws,
                         float* dw, float* db, hipStream_t st)
 {
-    static const hipError_t attr = hipFuncSetAttribute(
-        (const void*)k_wgrad<CIN, COUT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-        (int)(wgrad_lds(CIN, 16) > wgrad_lds(CIN, 64) ? wgrad_lds(CIN, 16) : wgrad_lds(CIN, 64)));
-    if (attr != hipSuccess) return attr;
     int columns, nch, zc;
     conv_chunks(n, batch, columns, nch, zc);
     const int blocks = columns * nch;
     float* wsb = ws + (size_t)blocks * 27 * 32 * 32;
-    hipLaunchKernelGGL((k_wgrad<CIN, COUT>), dim3(blocks), dim3(WG_THR), wgrad_lds(CIN, n), st,
-                       x, dz, n, ilog2(n), nch, zc, ws, wsb);
-    hipError_t e = hipGetLastError();
+    hipError_t e = n == 16   ? launch_wgrad_n<CIN, COUT, 4>(x, dz, blocks, nch, zc, ws, wsb, st)
+                   : n == 32 ? launch_wgrad_n<CIN, COUT, 5>(x, dz, blocks, nch, zc, ws, wsb, st)
+                             : launch_wgrad_n<CIN, COUT, 6>(x, dz, blocks, nch, zc, ws, wsb, st);
     if (e != hipSuccess) return e;
     const int total = COUT * 27 * CIN + COUT;
     hipLaunchKernelGGL(k_wgrad_reduce, dim3((total + RED_OUT - 1) / RED_OUT), dim3(NTHR), 0, st, ws,

@@ -71,3 +71,19 @@ def test_conv_infinite_input_reaches_its_neighbours_only(cin):
     nn.conv3d_fwd(x.to(torch.bfloat16), w_pad, torch.zeros(32, device="cuda"), n, 1, cin, 32, 1, y=y)
     ref = sum(v.sum(1, keepdim=True) for v in _taps(x, n, 1, cin)).expand(cells, 32)
     assert torch.equal(y.view(cells, 32), ref)
+
+
+@pytest.mark.parametrize("n,batch", [(16, 1), (16, 5), (32, 3), (64, 2)])
+@pytest.mark.parametrize("cin,cout", [(8, 8), (8, 32), (32, 8), (32, 32)])
+def test_weight_gradient_exact_on_whole_numbers(n, batch, cin, cout):
+    # every partial sum is a whole number below 16 * 2^19 < 2^24: exact in FP32
+    g = torch.Generator(device="cuda").manual_seed(n + batch + cin + cout)
+    cells = batch * n ** 3
+    x = torch.randint(-4, 5, (cells, cin), generator=g, device="cuda").float()
+    dz = torch.randint(-4, 5, (cells, cout), generator=g, device="cuda").float()
+    ws = torch.empty(nn.wgrad_workspace_floats(n, batch), device="cuda")
+    dw, db = _off(cout * 27 * cin, torch.float32), _off(cout, torch.float32)
+    nn.conv3d_wgrad(x.to(torch.bfloat16), dz.to(torch.bfloat16), n, batch, cin, cout, ws, dw, db)
+    ref = torch.stack([dz.t() @ v for v in _taps(x, n, batch, cin)], 1)
+    assert torch.equal(dw.view(cout, 27, cin), ref)
+    assert torch.equal(db, dz.sum(0))
