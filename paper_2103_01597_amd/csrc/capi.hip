@@ -30,8 +30,8 @@ struct mhd_ctx {
     hipEvent_t ev_ready;   // segmented step: a substep's segments are packed
     hipEvent_t ev_halo;    // segmented step: its halo has been unpacked
     int device;
-    double* red_partials;  // device, REDUCE_BLOCKS doubles, then 1 result
-    double* red_host;      // pinned host, 1 double
+    double* red_partials;  // device, REDUCE_BLOCKS doubles, then the counter of ended blocks
+    double* red_host;      // pinned host, 1 double (the reduction's kernel writes it)
 };
 
 namespace {
@@ -303,6 +303,9 @@ int mhd_init(const mhd_config* cfg, mhd_ctx** out, mhd_layout* layout)
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_halo, hipEventDisableTiming);
     if (e == hipSuccess) e = hipMalloc(&ctx->phys_dev, sizeof(Phys));
     if (e == hipSuccess) e = hipMemcpy(ctx->phys_dev, &ctx->phys, sizeof(Phys), hipMemcpyHostToDevice);
+    const double zero = 0.0;
+    if (e == hipSuccess)
+        e = hipMemcpy(ctx->red_partials + REDUCE_BLOCKS, &zero, sizeof zero, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipHostMalloc(&ctx->red_host, sizeof(double), hipHostMallocDefault);
     if (e != hipSuccess) {
         rc = from_hip(e);
@@ -460,10 +463,7 @@ int mhd_reduce(mhd_ctx* ctx, const void* fields, int32_t field, int32_t op, doub
     hipStream_t st = (hipStream_t)stream;
     const char* base = (const char*)fields + field * ctx->lay.field_stride * ctx->lay.elem_size;
     hipError_t e = launch_reduce(ctx->grid, base, (int)ctx->lay.elem_size, op, ctx->red_partials,
-                                 REDUCE_BLOCKS, ctx->red_partials + REDUCE_BLOCKS, st);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(ctx->red_host, ctx->red_partials + REDUCE_BLOCKS, sizeof(double),
-                           hipMemcpyDeviceToHost, st);
+                                 (unsigned*)(ctx->red_partials + REDUCE_BLOCKS), ctx->red_host, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return from_hip(e);
     *out_host = *ctx->red_host;

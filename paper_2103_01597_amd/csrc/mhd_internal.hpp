@@ -236,7 +236,7 @@ hipError_t launch_segments(const Grid& g, const SegTable& t, void* fields, void*
 
 
 hipError_t launch_reduce(const Grid& g, const void* field, int elem_size, int op,
-                         double* partials, int npartials, double* result, hipStream_t st);
+                         double* partials, unsigned* ended, double* result, hipStream_t st);
 
 constexpr int REDUCE_BLOCKS = 1024;
 

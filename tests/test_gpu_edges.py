@@ -1,10 +1,11 @@
-"""The convolutions at the edges of their tiles: every row length, one and many
-planes per block, both output widths, outputs that start off a vector boundary,
-and infinite inputs."""
+"""Kernels at the edges of their tiles.  Convolutions: every row length, one and
+many planes per block, both output widths, outputs that start off a vector
+boundary, infinite inputs.  Reductions: rows of one and several strides, fewer
+rows than blocks, remainders.  Substep: slabs of one to four planes."""
 import pytest
 import torch
 
-from paper_2103_01597_amd import nn
+from paper_2103_01597_amd import mhd, nn
 
 pytestmark = pytest.mark.gpu
 
@@ -87,3 +88,50 @@ def test_weight_gradient_exact_on_whole_numbers(n, batch, cin, cout):
     ref = torch.stack([dz.t() @ v for v in _taps(x, n, batch, cin)], 1)
     assert torch.equal(dw.view(cout, 27, cin), ref)
     assert torch.equal(db, dz.sum(0))
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32c"])
+@pytest.mark.parametrize("n", [(1, 1, 1), (300, 17, 5), (257, 3, 33), (8, 8, 200), (64, 64, 37), (513, 70, 40)])
+def test_reductions_exact_on_whole_numbers(n, prec):
+    # whole numbers below 2^53 in any order, twice (the second call finds what the first left)
+    S = mhd.Solver(*n, precision=prec)
+    f = S.zeros()
+    f += 1e6  # the halo is not part of it
+    g = torch.Generator(device="cuda").manual_seed(sum(n))
+    v = torch.randint(-1000, 1001, n[::-1], generator=g, device="cuda").double()
+    S.interior_view(f)[3].copy_(v)
+    for _ in range(2):
+        assert S.reduce(f, 3, "sum") == v.sum().item()
+        assert S.reduce(f, 3, "sumsq") == (v * v).sum().item()
+        assert S.reduce(f, 3, "maxabs") == v.abs().max().item()
+        assert S.reduce(f, 3, "min") == v.min().item()
+        assert S.reduce(f, 3, "max") == v.max().item()
+        assert S.reduce(f, 3, "nonfinite") == 0.0
+    S.interior_view(f)[3][-1, -1, -1] = float("nan")
+    assert S.reduce(f, 3, "nonfinite") == 1.0
+    assert S.reduce(f, 3, "min") != S.reduce(f, 3, "min")
+    S.close()
+
+
+@pytest.mark.parametrize("order", [2, 4, 6, 8])
+@pytest.mark.parametrize("prec", ["f64", "f32c", "f32"])
+def test_thin_slabs_equal_full_substep(prec, order):
+    # every cell's arithmetic is the same in any box: bit for bit
+    S = mhd.Solver(45, 19, 10, precision=prec, order=order)
+    g = torch.Generator(device="cuda").manual_seed(order)
+    f = torch.randn(S.layout.total_elems, generator=g, device="cuda", dtype=torch.float64) * 1e-2
+    f = f.to(S.torch_dtype)
+    S.halo_periodic(f)
+    old = torch.randn(f.numel(), generator=g, device="cuda").to(f) * 1e-3
+    comp = torch.randn(f.numel(), generator=g, device="cuda").to(f) * 1e-9 if prec == "f32c" else None
+    for s in (0, 1, 2):
+        got = []
+        for cuts in ((0, 10), (0, 1, 3, 6, 10)):
+            out, w, c = f.clone(), old.clone(), None if comp is None else comp.clone()
+            for a, b in zip(cuts, cuts[1:]):
+                S.rk3_substep_box(s, (0, 45, 0, 19, a, b), f, out, w, c)
+            got.append((out, w, c))
+        for full, thin in zip(*got):
+            assert full is None or torch.equal(full, thin)
+        assert bool(torch.isfinite(got[0][0]).all())
+    S.close()
