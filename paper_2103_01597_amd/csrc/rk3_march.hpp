@@ -100,15 +100,20 @@ constexpr size_t ring_bytes()
 {
     return sizeof(typename Prec<PREC>::T) * SRing<PREC, RAD>::NSLOT * SRing<PREC, RAD>::SLOT;
 }
-// One workgroup per CU: more than half of the 160 KB is asked for where the
-// ring is smaller.  (FP64 at r = 1 would fit two; with both resident their
-// halo reads find less in L2: 3240 against 3150 us per step at 256^3.)
+// Whether two workgroups share a CU: plain FP32 up to r = 3, whose rings and
+// registers (124, held to 128 at r = 2) allow it.  us per step at 256^3 with one
+// and two: orders 2, 4, 6 1890 -> 1735, 1873 -> 1830, 1973 -> 1878.
+// The other precisions fit two at r = 1 only and lose by it, as the halo reads
+// of two tiles find less in L2: FP64 3150 -> 3240, FP32C 2440 -> 2567.  They
+// ask for more than half of the 160 KB where the ring is smaller.
+template <int PREC, int RAD>
+constexpr bool two_resident() { return PREC == MHD_F32 && RAD <= 3; }
 template <int PREC, int RAD>
 constexpr size_t lds_bytes()
 {
     constexpr size_t need = ring_bytes<PREC, RAD>() +
                             sizeof(typename Prec<PREC>::Rt) * (nxf<PREC>() + nxm<PREC>()) * SRing<PREC, RAD>::NC;
-    return need > 84 * 1024 ? need : 84 * 1024;
+    return two_resident<PREC, RAD>() || need > 84 * 1024 ? need : 84 * 1024;
 }
 
 static_assert(SRing<MHD_F64, 4>::NC % 64 == 0 && SRing<MHD_F32, 1>::NC % 64 == 0,
@@ -208,7 +213,7 @@ __device__ __forceinline__ void rhs_entropy_other(const Phys& P, const EntropyOw
 // guarantees that every pair is aligned (even padded row length, even box x0,
 // aligned f_in).
 template <int PREC, int RAD, bool MULTI, bool PAIRS>
-__global__ __launch_bounds__((SRing<PREC, RAD>::NTH), 1) void k_rk3_split(Grid g, const Phys* __restrict__ P_dev, Scales<RAD> sc, TileMap map, int s,
+__global__ __launch_bounds__((SRing<PREC, RAD>::NTH), (two_resident<PREC, RAD>() ? 4 : 1)) void k_rk3_split(Grid g, const Phys* __restrict__ P_dev, Scales<RAD> sc, TileMap map, int s,
                                                      const typename Prec<PREC>::T* __restrict__ fin,
                                                      typename Prec<PREC>::T* __restrict__ fout,
                                                      typename Prec<PREC>::T* __restrict__ w,
