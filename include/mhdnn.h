@@ -107,6 +107,14 @@ int mhdnn_conv3d_wgrad_noalloc(const uint16_t *x, const uint16_t *dz, int32_t n,
 int mhdnn_prepare_weights(const float *w, int32_t cin, int32_t cout, uint16_t *w_pad,
                           uint16_t *wt_pad, void *stream);
 
+/* mhdnn_prepare_weights of `count` (0..8) layers in one launch. */
+typedef struct {
+    const float *w;
+    uint16_t *w_pad, *wt_pad; /* wt_pad may be NULL */
+    int32_t cin, cout;
+} mhdnn_weights_part;
+int mhdnn_prepare_weights_parts(const mhdnn_weights_part *parts, int32_t count, void *stream);
+
 /* Mean-squared error of one batch: y is the network output, channels-last
  * [b][cell][q] (batch * n^3 * 8 floats); the target is field-major
  * [b][q][cell] (the layout of mhdnn_pair's d) times tscale[q] (8 host
@@ -140,6 +148,16 @@ int mhdnn_field_stats(const float *x, int64_t npairs, int64_t n3, double *worksp
  * p -= lr (m / (1 - b1^t)) / (sqrt(v / (1 - b2^t)) + eps).  t >= 1. */
 int mhdnn_adam(float *p, const float *g, float *m, float *v, int64_t n, float lr, float b1,
                float b2, float eps, int32_t t, void *stream);
+
+/* mhdnn_adam of `count` (0..8) disjoint parameter arrays in one launch. */
+typedef struct {
+    float *p;
+    const float *g;
+    float *m, *v;
+    int64_t n;
+} mhdnn_adam_part;
+int mhdnn_adam_parts(const mhdnn_adam_part *parts, int32_t count, float lr, float b1, float b2,
+                     float eps, int32_t t, void *stream);
 
 /* Add a network correction to the interior of a coarse solver state:
  * f[q][cell] += y[cell][q] * scale[q] (scale: 8 host floats), with the

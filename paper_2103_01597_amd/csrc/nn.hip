@@ -637,17 +637,55 @@ __global__ __launch_bounds__(NTHR) void k_wgrad_reduce(const float* __restrict__
 }
 
 // ------------------------------------------------------------ elementwise
-__global__ void k_prepare_weights(const float* __restrict__ w, int cin, int cout,
-                                  uint16_t* __restrict__ wpad, uint16_t* __restrict__ wtpad)
+// Several arrays in one launch: launches, not work, are what a training step's
+// updates of six small arrays and preparations of three layers cost: nine
+// launches, two now (backward pass at 4 x 64^3 308 -> 298 us).  Block b serves the part whose blocks begin at
+// or before b (uniform).
+constexpr int MAX_PARTS = 8;
+template <typename P>
+struct Parts {
+    P part[MAX_PARTS];
+    int first[MAX_PARTS + 1];  // first block of each part, then their number
+};
+template <typename P>
+__device__ __forceinline__ P part_of_block(const Parts<P>& s, int& block)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < 32 * 27 * cin) {  // wpad[o][t][c]
-        const int o = i / (27 * cin), rem = i - o * 27 * cin;
-        wpad[i] = o < cout ? f2bf(w[o * 27 * cin + rem]) : (uint16_t)0;
+    int k = 0;
+#pragma unroll
+    for (int q = 1; q < MAX_PARTS; ++q) k += (int)blockIdx.x >= s.first[q];
+    block = blockIdx.x - s.first[k];
+    return s.part[k];
+}
+// blocks(part) blocks each; parts past count get none
+template <typename P, typename F>
+Parts<P> make_parts(const P* parts, int count, F blocks)
+{
+    Parts<P> s{};
+    int at = 0;
+    for (int k = 0; k < MAX_PARTS; ++k) {
+        s.first[k] = at;
+        if (k < count) {
+            s.part[k] = parts[k];
+            at += blocks(parts[k]);
+        }
     }
-    if (wtpad && i < 32 * 27 * cout) {  // wtpad[c][t][o] = w[o][26 - t][c]
+    s.first[MAX_PARTS] = at;
+    return s;
+}
+
+__global__ void k_prepare_weights(Parts<mhdnn_weights_part> s)
+{
+    int block;
+    const mhdnn_weights_part a = part_of_block(s, block);
+    const float* __restrict__ w = a.w;
+    const int cin = a.cin, cout = a.cout, i = block * blockDim.x + threadIdx.x;
+    if (i < 32 * 27 * cin) {  // w_pad[o][t][c]
+        const int o = i / (27 * cin), rem = i - o * 27 * cin;
+        a.w_pad[i] = o < cout ? f2bf(w[o * 27 * cin + rem]) : (uint16_t)0;
+    }
+    if (a.wt_pad && i < 32 * 27 * cout) {  // wt_pad[c][t][o] = w[o][26 - t][c]
         const int c = i / (27 * cout), rem = i - c * 27 * cout, t = rem / cout, o = rem - t * cout;
-        wtpad[i] = c < cin ? f2bf(w[(o * 27 + (26 - t)) * cin + c]) : (uint16_t)0;
+        a.wt_pad[i] = c < cin ? f2bf(w[(o * 27 + (26 - t)) * cin + c]) : (uint16_t)0;
     }
 }
 
@@ -840,18 +878,19 @@ __global__ void k_stats_final(const double* __restrict__ partials, double count,
     out[q] = root ? sqrt(s) : s;
 }
 
-__global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                       float* __restrict__ v, int64_t n, float lr, float b1, float b2, float eps,
-                       float c1, float c2)
+__global__ void k_adam(Parts<mhdnn_adam_part> s, float lr, float b1, float b2, float eps, float c1,
+                       float c2)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    int block;
+    const mhdnn_adam_part a = part_of_block(s, block);
+    const int64_t i = (int64_t)block * blockDim.x + threadIdx.x;
+    if (i >= a.n) return;
+    const float gi = a.g[i];
+    const float mi = b1 * a.m[i] + (1.0f - b1) * gi;
+    const float vi = b2 * a.v[i] + (1.0f - b2) * gi * gi;
+    a.m[i] = mi;
+    a.v[i] = vi;
+    a.p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
 int ilog2(int n)
@@ -1108,10 +1147,24 @@ int mhdnn_conv3d_wgrad_noalloc(const uint16_t* x, const uint16_t* dz, int32_t n,
 int mhdnn_prepare_weights(const float* w, int32_t cin, int32_t cout, uint16_t* w_pad,
                           uint16_t* wt_pad, void* stream)
 {
-    if (!w || !w_pad || (cin != 8 && cin != 32) || (cout != 8 && cout != 32)) return MHD_ERR_INVALID;
-    const int total = 32 * 27 * 32;
-    hipLaunchKernelGGL(k_prepare_weights, dim3((total + 255) / 256), dim3(256), 0,
-                       (hipStream_t)stream, w, cin, cout, w_pad, wt_pad);
+    const mhdnn_weights_part one = {w, w_pad, wt_pad, cin, cout};
+    return mhdnn_prepare_weights_parts(&one, 1, stream);
+}
+
+int mhdnn_prepare_weights_parts(const mhdnn_weights_part* parts, int32_t count, void* stream)
+{
+    if (!parts || count < 0 || count > MAX_PARTS) return MHD_ERR_INVALID;
+    for (int k = 0; k < count; ++k) {
+        const mhdnn_weights_part& a = parts[k];
+        if (!a.w || !a.w_pad || (a.cin != 8 && a.cin != 32) || (a.cout != 8 && a.cout != 32))
+            return MHD_ERR_INVALID;
+    }
+    if (count == 0) return MHD_OK;
+    const auto set = make_parts(parts, count, [](const mhdnn_weights_part& a) {
+        return (32 * 27 * (a.cin > a.cout ? a.cin : a.cout) + 255) / 256;
+    });
+    hipLaunchKernelGGL(k_prepare_weights, dim3(set.first[MAX_PARTS]), dim3(256), 0,
+                       (hipStream_t)stream, set);
     return status(hipGetLastError());
 }
 
@@ -1164,11 +1217,28 @@ int mhdnn_field_stats(const float* x, int64_t npairs, int64_t n3, double* worksp
 int mhdnn_adam(float* p, const float* g, float* m, float* v, int64_t n, float lr, float b1,
                float b2, float eps, int32_t t, void* stream)
 {
-    if (!p || !g || !m || !v || n < 0 || t < 1) return MHD_ERR_INVALID;
-    if (n == 0) return MHD_OK;
+    const mhdnn_adam_part one = {p, g, m, v, n};
+    return mhdnn_adam_parts(&one, 1, lr, b1, b2, eps, t, stream);
+}
+
+int mhdnn_adam_parts(const mhdnn_adam_part* parts, int32_t count, float lr, float b1, float b2,
+                     float eps, int32_t t, void* stream)
+{
+    if (!parts || count < 0 || count > MAX_PARTS || t < 1) return MHD_ERR_INVALID;
+    int64_t blocks = 0;
+    for (int k = 0; k < count; ++k) {
+        const mhdnn_adam_part& a = parts[k];
+        if (!a.p || !a.g || !a.m || !a.v || a.n < 0) return MHD_ERR_INVALID;
+        blocks += a.n / 256 + (a.n % 256 != 0);
+        if (blocks > INT32_MAX) return MHD_ERR_INVALID;  // more than 2 TB of parameters
+    }
+    if (blocks == 0) return MHD_OK;
     const float c1 = 1.0f - powf(b1, (float)t), c2 = 1.0f - powf(b2, (float)t);
-    hipLaunchKernelGGL(k_adam, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                       (hipStream_t)stream, p, g, m, v, n, lr, b1, b2, eps, c1, c2);
+    const auto set = make_parts(parts, count, [](const mhdnn_adam_part& a) {
+        return (int)(a.n / 256 + (a.n % 256 != 0));
+    });
+    hipLaunchKernelGGL(k_adam, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, set, lr,
+                       b1, b2, eps, c1, c2);
     return status(hipGetLastError());
 }
 

@@ -15,10 +15,23 @@ from . import mhd as _mhd
 
 EXPORTS = ("mhdnn_box_filter4", "mhdnn_pack", "mhdnn_conv3d_fwd", "mhdnn_conv3d_dgrad",
            "mhdnn_wgrad_workspace_floats", "mhdnn_conv3d_wgrad", "mhdnn_prepare_weights",
+           "mhdnn_prepare_weights_parts", "mhdnn_adam_parts",
            "mhdnn_mse", "mhdnn_pair", "mhdnn_field_stats_workspace_doubles",
            "mhdnn_field_stats", "mhdnn_adam", "mhdnn_apply", "mhdnn_conv3d_wgrad_noalloc")
 _INT64_RESULT = ("mhdnn_wgrad_workspace_floats", "mhdnn_field_stats_workspace_doubles")
 LAYERS = ((8, 32, True), (32, 32, True), (32, 8, False))  # (cin, cout, gelu)
+
+
+
+class WeightsPart(ctypes.Structure):
+    _fields_ = [("w", ctypes.c_void_p), ("w_pad", ctypes.c_void_p), ("wt_pad", ctypes.c_void_p),
+                ("cin", ctypes.c_int32), ("cout", ctypes.c_int32)]
+
+
+class AdamPart(ctypes.Structure):
+    _fields_ = [("p", ctypes.c_void_p), ("g", ctypes.c_void_p), ("m", ctypes.c_void_p),
+                ("v", ctypes.c_void_p), ("n", ctypes.c_int64)]
+
 
 _bound = False
 
@@ -45,6 +58,8 @@ def lib():
     L.mhdnn_field_stats_workspace_doubles.restype = i64
     L.mhdnn_field_stats.argtypes = [vp, i64, i64, vp, vp, vp]
     L.mhdnn_adam.argtypes = [vp, vp, vp, vp, i64, f32, f32, f32, f32, i32, vp]
+    L.mhdnn_prepare_weights_parts.argtypes = [ctypes.POINTER(WeightsPart), i32, vp]
+    L.mhdnn_adam_parts.argtypes = [ctypes.POINTER(AdamPart), i32, f32, f32, f32, f32, i32, vp]
     L.mhdnn_apply.argtypes = [vp, vp, vp, vp, fp, vp, vp]
     for fn in EXPORTS:
         if fn not in _INT64_RESULT:
@@ -115,6 +130,13 @@ def prepare_weights(w, cin, cout, w_pad, wt_pad=None, stream=None):
                                                               _p(wt_pad), _st(stream)))
 
 
+def prepare_weights_parts(parts, stream=None):
+    """parts: up to 8 of (w, cin, cout, w_pad, wt_pad or None)."""
+    arr = (WeightsPart * max(len(parts), 1))(*[WeightsPart(_p(w), _p(wp), _p(wt), cin, cout)
+                                       for w, cin, cout, wp, wt in parts])
+    _chk("mhdnn_prepare_weights_parts", lib().mhdnn_prepare_weights_parts(arr, len(parts), _st(stream)))
+
+
 def mse(y, target, tscale, n, batch, dy, partials, stream=None):
     """target: field-major [batch][8][n^3] FP32, scaled per field by tscale."""
     _chk("mhdnn_mse", lib().mhdnn_mse(_p(y), _p(target), _f8(tscale), n, batch, _p(dy),
@@ -141,6 +163,13 @@ def field_stats(x, npairs, n3, stream=None):
 def adam(p, g, m, v, lr, t, b1=0.9, b2=0.999, eps=1e-8, stream=None):
     _chk("mhdnn_adam", lib().mhdnn_adam(_p(p), _p(g), _p(m), _p(v), p.numel(), lr, b1, b2, eps, t,
                                         _st(stream)))
+
+
+def adam_parts(parts, lr, t, b1=0.9, b2=0.999, eps=1e-8, stream=None):
+    """parts: up to 8 of (p, g, m, v), disjoint."""
+    arr = (AdamPart * max(len(parts), 1))(*[AdamPart(_p(p), _p(g), _p(m), _p(v), p.numel())
+                                    for p, g, m, v in parts])
+    _chk("mhdnn_adam_parts", lib().mhdnn_adam_parts(arr, len(parts), lr, b1, b2, eps, t, _st(stream)))
 
 
 def apply(solver, fields, comp, y, scale, guard=None, stream=None):
@@ -172,8 +201,8 @@ class Closure:
         self.refresh()
 
     def refresh(self):
-        for (cin, cout, _), w, wp, wt in zip(LAYERS, self.w, self.w_pad, self.wt_pad):
-            prepare_weights(w, cin, cout, wp, wt)
+        prepare_weights_parts([(w, cin, cout, wp, wt) for (cin, cout, _), w, wp, wt
+                               in zip(LAYERS, self.w, self.w_pad, self.wt_pad)])
 
     def forward(self, x, n, batch):
         """x: BF16 [batch*n^3*8]; returns FP32 y [batch*n^3*8] and the cache."""
@@ -220,6 +249,6 @@ class Closure:
 
     def step(self, grads, lr):
         self.t += 1
-        for p, g, m, v in zip(self.params, grads, self.m, self.v):
-            adam(p, g.contiguous(), m, v, lr, self.t)
+        adam_parts([(p, g.contiguous(), m, v) for p, g, m, v
+                    in zip(self.params, grads, self.m, self.v)], lr, self.t)
         self.refresh()

@@ -1,7 +1,8 @@
 """Kernels at the edges of their tiles.  Convolutions: every row length, one and
 many planes per block, both output widths, outputs that start off a vector
 boundary, infinite inputs.  Reductions: rows of one and several strides, fewer
-rows than blocks, remainders.  Substep: slabs of one to four planes."""
+rows than blocks, remainders.  Substep: slabs of one to four planes.  Optimizer: arrays of
+unequal sizes in one launch."""
 import pytest
 import torch
 
@@ -135,3 +136,28 @@ def test_thin_slabs_equal_full_substep(prec, order):
             assert full is None or torch.equal(full, thin)
         assert bool(torch.isfinite(got[0][0]).all())
     S.close()
+
+
+@pytest.mark.parametrize("sizes", [(1,), (256, 1), (6912, 32, 27648, 0, 6912, 8), (257, 255, 256, 1, 2, 3, 4, 5)])
+def test_updates_in_one_launch_equal_one_by_one(sizes):
+    g = torch.Generator(device="cuda").manual_seed(len(sizes))
+    parts = [tuple(torch.rand(n + 1, generator=g, device="cuda")[1:] for _ in range(4)) for n in sizes if n]
+    alone = [tuple(t.clone() for t in q) for q in parts]
+    for t in (1, 2):
+        nn.adam_parts(parts, 1e-3, t)
+        for p, gr, m, v in alone:
+            nn.adam(p, gr, m, v, 1e-3, t)
+    for a, b in zip(parts, alone):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
+    pads = []
+    for cin, cout in ((8, 8), (8, 32), (32, 32), (32, 8)):
+        w = torch.randn(cout, 27, cin, generator=g, device="cuda")
+        pads.append((w, cin, cout) + tuple(torch.full((32 * 27 * c,), 7.0, dtype=torch.bfloat16, device="cuda") for c in (cin, cout)))
+    nn.prepare_weights_parts(pads)
+    for w, cin, cout, wp, wt in pads:
+        wide = torch.zeros(32, 27, cin, device="cuda")
+        wide[:cout] = w
+        assert torch.equal(wp.view(32, 27, cin), wide.to(torch.bfloat16))
+        flip = torch.zeros(32, 27, cout, device="cuda")
+        flip[:cin] = w.flip(1).permute(2, 1, 0)
+        assert torch.equal(wt.view(32, 27, cout), flip.to(torch.bfloat16))
