@@ -30,8 +30,7 @@ struct mhd_ctx {
     hipEvent_t ev_ready;   // segmented step: a substep's segments are packed
     hipEvent_t ev_halo;    // segmented step: its halo has been unpacked
     int device;
-    double* red_partials;  // device, REDUCE_BLOCKS doubles, then the counter of ended blocks
-    double* red_host;      // pinned host, 1 double (the reduction's kernel writes it)
+    double* red_partials;  // pinned host, REDUCE_BLOCKS doubles (a reduction's blocks write them)
 };
 
 namespace {
@@ -297,16 +296,12 @@ int mhd_init(const mhd_config* cfg, mhd_ctx** out, mhd_layout* layout)
     P.cp_gm1 = cfg->cp * (cfg->gamma - 1.0);
     P.hc = cfg->heat - cfg->cool;
 
-    hipError_t e = hipMalloc(&ctx->red_partials, (REDUCE_BLOCKS + 1) * sizeof(double));
+    hipError_t e = hipHostMalloc(&ctx->red_partials, REDUCE_BLOCKS * sizeof(double), hipHostMallocDefault);
     ctx->seg = seg_table(ctx->grid);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_ready, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_halo, hipEventDisableTiming);
     if (e == hipSuccess) e = hipMalloc(&ctx->phys_dev, sizeof(Phys));
     if (e == hipSuccess) e = hipMemcpy(ctx->phys_dev, &ctx->phys, sizeof(Phys), hipMemcpyHostToDevice);
-    const double zero = 0.0;
-    if (e == hipSuccess)
-        e = hipMemcpy(ctx->red_partials + REDUCE_BLOCKS, &zero, sizeof zero, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipHostMalloc(&ctx->red_host, sizeof(double), hipHostMallocDefault);
     if (e != hipSuccess) {
         rc = from_hip(e);
         mhd_finalize(ctx);
@@ -320,11 +315,10 @@ int mhd_init(const mhd_config* cfg, mhd_ctx** out, mhd_layout* layout)
 void mhd_finalize(mhd_ctx* ctx)
 {
     if (!ctx) return;
-    if (ctx->red_partials) (void)hipFree(ctx->red_partials);
+    if (ctx->red_partials) (void)hipHostFree(ctx->red_partials);
     if (ctx->phys_dev) (void)hipFree(ctx->phys_dev);
     if (ctx->ev_ready) (void)hipEventDestroy(ctx->ev_ready);
     if (ctx->ev_halo) (void)hipEventDestroy(ctx->ev_halo);
-    if (ctx->red_host) (void)hipHostFree(ctx->red_host);
     delete ctx;
 }
 
@@ -462,11 +456,10 @@ int mhd_reduce(mhd_ctx* ctx, const void* fields, int32_t field, int32_t op, doub
         return MHD_ERR_INVALID;
     hipStream_t st = (hipStream_t)stream;
     const char* base = (const char*)fields + field * ctx->lay.field_stride * ctx->lay.elem_size;
-    hipError_t e = launch_reduce(ctx->grid, base, (int)ctx->lay.elem_size, op, ctx->red_partials,
-                                 (unsigned*)(ctx->red_partials + REDUCE_BLOCKS), ctx->red_host, st);
+    hipError_t e = launch_reduce(ctx->grid, base, (int)ctx->lay.elem_size, op, ctx->red_partials, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return from_hip(e);
-    *out_host = *ctx->red_host;
+    *out_host = combine_partials(ctx->red_partials, reduce_blocks(ctx->grid), op);
     return MHD_OK;
 }
 

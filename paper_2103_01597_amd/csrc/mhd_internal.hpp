@@ -235,9 +235,12 @@ hipError_t launch_segments(const Grid& g, const SegTable& t, void* fields, void*
                            int elem_size, bool unpack, hipStream_t st);
 
 
-hipError_t launch_reduce(const Grid& g, const void* field, int elem_size, int op,
-                         double* partials, unsigned* ended, double* result, hipStream_t st);
-
-constexpr int REDUCE_BLOCKS = 1024;
+// Reductions: the blocks' partials into pinned host memory, and their combination
+// there once the launch has ended.
+constexpr int REDUCE_BLOCKS = 1024;  // at most
+int reduce_blocks(const Grid& g);
+hipError_t launch_reduce(const Grid& g, const void* field, int elem_size, int op, double* partials,
+                         hipStream_t st);
+double combine_partials(const double* partials, int n, int op);
 
 }  // namespace mhd

@@ -1,33 +1,38 @@
 // Deterministic reductions over the interior of one field, in one launch.
 // Block b walks rows b, b + G, b + 2G, ... (G blocks) with each thread
-// striding x by 256, then a fixed LDS tree; the block that ends last combines
-// the G partials in the same fixed tree and writes the result to the host.
-// FP64 accumulation throughout, so the result depends only on the data, never
-// on timing.
+// striding x by 256, then a fixed LDS tree, and writes its partial to pinned host
+// memory; once the launch has ended the host combines the G partials in the same
+// fixed tree (combine_partials).  FP64 accumulation throughout, so the result
+// depends only on the data, never on timing, and nothing is kept from one call for
+// the next: every partial that is read was written by the call's own launch.
 //
 // Bound by memory latency where a thread waits for each value before it fetches
-// the next (256^3 FP64: 53 us, 2.5 TB/s), so RED_AHEAD values are fetched at a
-// time and then added in the same order: 32 us, 4.2 TB/s (8 at a time: 33).  A
-// second launch for the partials and a copy of the result cost 14 us more, with
-// the gaps between them.
+// the next, so RED_AHEAD values are fetched at a time and then added in the same
+// order (8 at a time: 3% slower at 256^3).  A call at 256^3 and 32^3, FP64: 58 and 23 us
+// with one value at a time, a second launch for the partials and a copy of the result;
+// 44 and 31 with the block that ends last combining the partials, which takes a count of
+// ended blocks (one address for all of them, and a value that outlives the call);
+// 38 and 21 now.
+#include <math.h>
+
 #include "mhd_internal.hpp"
 
 namespace mhd {
 namespace {
 
-__device__ __forceinline__ double nan_max(double a, double b)
+__host__ __device__ __forceinline__ double nan_max(double a, double b)
 {
-    return (isnan(a) || isnan(b)) ? __longlong_as_double(0x7ff8000000000000LL) : (a > b ? a : b);
+    return (isnan(a) || isnan(b)) ? __builtin_nan("") : (a > b ? a : b);
 }
-__device__ __forceinline__ double nan_min(double a, double b)
+__host__ __device__ __forceinline__ double nan_min(double a, double b)
 {
-    return (isnan(a) || isnan(b)) ? __longlong_as_double(0x7ff8000000000000LL) : (a < b ? a : b);
+    return (isnan(a) || isnan(b)) ? __builtin_nan("") : (a < b ? a : b);
 }
 
-__device__ __forceinline__ double red_init(int op)
+__host__ __device__ __forceinline__ double red_init(int op)
 {
-    if (op == MHD_RED_MIN) return __longlong_as_double(0x7ff0000000000000LL);   // +inf
-    if (op == MHD_RED_MAX) return -__longlong_as_double(0x7ff0000000000000LL);  // -inf
+    if (op == MHD_RED_MIN) return __builtin_huge_val();
+    if (op == MHD_RED_MAX) return -__builtin_huge_val();
     return 0.0;
 }
 __device__ __forceinline__ double red_map(double v, int op)
@@ -40,7 +45,7 @@ __device__ __forceinline__ double red_map(double v, int op)
     default: return v;
     }
 }
-__device__ __forceinline__ double red_comb(double a, double b, int op)
+__host__ __device__ __forceinline__ double red_comb(double a, double b, int op)
 {
     switch (op) {
     case MHD_RED_MAXABS:
@@ -50,12 +55,14 @@ __device__ __forceinline__ double red_comb(double a, double b, int op)
     }
 }
 
+constexpr int RED_THR = 256;
+
 __device__ double block_tree(double v, int op, double* sh)
 {
     const int t = threadIdx.x;
     sh[t] = v;
     __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
+    for (int h = RED_THR / 2; h > 0; h >>= 1) {
         if (t < h)
             sh[t] = red_comb(sh[t], sh[t + h], op);
         __syncthreads();
@@ -66,11 +73,10 @@ __device__ double block_tree(double v, int op, double* sh)
 constexpr int RED_AHEAD = 16;
 
 template <typename E, int op>
-__global__ __launch_bounds__(256) void k_reduce(Grid g, const E* __restrict__ f, double* partials,
-                                                unsigned* ended, double* out)
+__global__ __launch_bounds__(RED_THR) void k_reduce(Grid g, const E* __restrict__ f,
+                                                    double* __restrict__ partials)
 {
-    __shared__ double sh[256];
-    __shared__ bool last;
+    __shared__ double sh[RED_THR];
     double acc = red_init(op);
     const int G = gridDim.x, rows = g.ny * g.nz, t = threadIdx.x;
     const int dj = G % g.ny, dk = G / g.ny;
@@ -83,7 +89,7 @@ __global__ __launch_bounds__(256) void k_reduce(Grid g, const E* __restrict__ f,
         for (int u = 0; u < RED_AHEAD; ++u) {
             ok[u] = r < rows;  // past the end the first cell stands in
             v[u] = f[g.interior + (ok[u] ? (int64_t)k * g.mxy + j * g.mx + x : 0)];
-            x += 256;
+            x += RED_THR;
             if (x >= g.nx) {
                 x = t;
                 r += G;
@@ -102,35 +108,15 @@ __global__ __launch_bounds__(256) void k_reduce(Grid g, const E* __restrict__ f,
         }
     }
     const double b = block_tree(acc, op, sh);
-    if (t == 0) {
-        __hip_atomic_store(partials + blockIdx.x, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // The partial has reached memory before the count does.  (Both bypass the
-        // caches that are not shared, so no cache is written back or
-        // invalidated for this; an acquire-release count does that in every
-        // block, and the launch takes 66 us instead of 32.)
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        last = __hip_atomic_fetch_add(ended, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == G - 1u;
-    }
-    __syncthreads();
-    if (!last) return;
-    acc = red_init(op);
-    for (int i = t; i < G; i += 256)
-        acc = red_comb(acc, __hip_atomic_load(partials + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), op);
-    const double total = block_tree(acc, op, sh);
-    if (t == 0) {
-        __hip_atomic_store(ended, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
-        __hip_atomic_store(out, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+    if (t == 0) partials[blockIdx.x] = b;
 }
 
 template <typename E>
-hipError_t launch_typed(const Grid& g, const E* f, int op, double* partials, unsigned* ended,
-                        double* out, hipStream_t st)
+hipError_t launch_typed(const Grid& g, const E* f, int op, double* partials, hipStream_t st)
 {
-    const int64_t rows = (int64_t)g.ny * g.nz;
-    const dim3 grid((unsigned)(rows < REDUCE_BLOCKS ? rows : REDUCE_BLOCKS));
+    const dim3 grid(reduce_blocks(g));
 #define MHD_REDUCE(OP) \
-    case OP: hipLaunchKernelGGL((k_reduce<E, OP>), grid, dim3(256), 0, st, g, f, partials, ended, out); break
+    case OP: hipLaunchKernelGGL((k_reduce<E, OP>), grid, dim3(RED_THR), 0, st, g, f, partials); break
     switch (op) {
         MHD_REDUCE(MHD_RED_SUM);
         MHD_REDUCE(MHD_RED_SUMSQ);
@@ -147,14 +133,32 @@ hipError_t launch_typed(const Grid& g, const E* f, int op, double* partials, uns
 
 }  // namespace
 
-// partials: REDUCE_BLOCKS doubles of device memory; ended: a device counter
-// that is zero before and after; result: memory of the host that the device
-// writes.  Launches that share them must not overlap.
-hipError_t launch_reduce(const Grid& g, const void* field, int elem_size, int op, double* partials,
-                         unsigned* ended, double* result, hipStream_t st)
+int reduce_blocks(const Grid& g)
 {
-    return elem_size == 8 ? launch_typed(g, (const double*)field, op, partials, ended, result, st)
-                          : launch_typed(g, (const float*)field, op, partials, ended, result, st);
+    const int64_t rows = (int64_t)g.ny * g.nz;
+    return (int)(rows < REDUCE_BLOCKS ? rows : REDUCE_BLOCKS);
+}
+
+// partials: reduce_blocks(g) doubles of pinned host memory
+hipError_t launch_reduce(const Grid& g, const void* field, int elem_size, int op, double* partials,
+                         hipStream_t st)
+{
+    return elem_size == 8 ? launch_typed(g, (const double*)field, op, partials, st)
+                          : launch_typed(g, (const float*)field, op, partials, st);
+}
+
+// As one block of RED_THR threads would: thread t takes partials t, t + RED_THR, ..., then
+// the tree of block_tree.
+double combine_partials(const double* partials, int n, int op)
+{
+    double v[RED_THR];
+    for (int t = 0; t < RED_THR; ++t) {
+        v[t] = red_init(op);
+        for (int i = t; i < n; i += RED_THR) v[t] = red_comb(v[t], partials[i], op);
+    }
+    for (int h = RED_THR / 2; h > 0; h >>= 1)
+        for (int t = 0; t < h; ++t) v[t] = red_comb(v[t], v[t + h], op);
+    return v[0];
 }
 
 }  // namespace mhd

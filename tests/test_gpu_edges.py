@@ -3,6 +3,8 @@ many planes per block, both output widths, outputs that start off a vector
 boundary, infinite inputs.  Reductions: rows of one and several strides, fewer
 rows than blocks, remainders.  Substep: slabs of one to four planes.  Optimizer: arrays of
 unequal sizes in one launch."""
+import threading
+
 import pytest
 import torch
 
@@ -111,6 +113,32 @@ def test_reductions_exact_on_whole_numbers(n, prec):
     S.interior_view(f)[3][-1, -1, -1] = float("nan")
     assert S.reduce(f, 3, "nonfinite") == 1.0
     assert S.reduce(f, 3, "min") != S.reduce(f, 3, "min")
+    S.close()
+
+
+@pytest.mark.parametrize("n", [(32, 32, 32), (64, 64, 64), (9, 3, 5)])
+def test_reductions_leave_nothing_behind(n):
+    # one context used by several threads at once has no defined values, but whatever
+    # such calls do must not reach the calls after them
+    S = mhd.Solver(*n)
+    f = S.zeros()
+    v = torch.arange(n[0] * n[1] * n[2], device="cuda").double().view(n[::-1])
+    S.interior_view(f)[0].copy_(v)
+    torch.cuda.synchronize()
+
+    def many(stream):
+        for _ in range(50):
+            S.reduce(f, 0, "sum", stream=stream)
+
+    threads = [threading.Thread(target=many, args=(torch.cuda.Stream(),)) for _ in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for op, want in (("sum", v.sum().item()), ("max", v.max().item()), ("min", 0.0), ("nonfinite", 0.0)):
+        assert S.reduce(f, 0, op) == want
+    S.interior_view(f)[0].add_(1.0)
+    assert S.reduce(f, 0, "min") == 1.0
     S.close()
 
 
