@@ -1,6 +1,6 @@
 """Kernels at the edges of their tiles.  Convolutions: every row length, one and
 many planes per block, both output widths, outputs that start off a vector
-boundary, infinite inputs.  Reductions: rows of one and several strides, fewer
+boundary, infinite inputs.  Halo fill: rows of any length and start.  Reductions: rows of one and several strides, fewer
 rows than blocks, remainders.  Substep: slabs of one to four planes.  Optimizer: arrays of
 unequal sizes in one launch."""
 import threading
@@ -91,6 +91,29 @@ def test_weight_gradient_exact_on_whole_numbers(n, batch, cin, cout):
     ref = torch.stack([dz.t() @ v for v in _taps(x, n, batch, cin)], 1)
     assert torch.equal(dw.view(cout, 27, cin), ref)
     assert torch.equal(db, dz.sum(0))
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("n,order", [((1, 1, 1), 8), ((2, 3, 5), 8), ((1, 40, 70), 2), ((16, 16, 16), 6), ((17, 15, 33), 6),
+                                     ((30, 5, 9), 4), ((31, 64, 3), 2), ((65, 33, 8), 8), ((2500, 3, 2), 6), ((9001, 2, 1), 6)])
+def test_halo_fill_of_any_row(n, order, prec, offset):
+    # rows of any length, in whole and broken units, from aligned and other addresses:
+    # padded coordinate s holds the interior cell (s - r) mod n, nothing else changes
+    S = mhd.Solver(*n, prec, order=order)
+    g = torch.Generator(device="cuda").manual_seed(sum(n))
+    total = S.layout.total_elems
+    room = torch.randn(total + 16, generator=g, device="cuda", dtype=torch.float64).to(S.torch_dtype)
+    f = room[offset:offset + total]
+    before = room.clone()
+    want = S.interior_view(f).clone()
+    for axis, m in ((3, n[0]), (2, n[1]), (1, n[2])):
+        want = want.index_select(axis, (torch.arange(m + 2 * S.r, device="cuda") - S.r) % m)
+    S.halo_periodic(f)
+    assert torch.equal(S.grid_view(f), want)
+    S.grid_view(f).copy_(S.grid_view(before[offset:offset + total]))
+    assert torch.equal(room, before)
+    S.close()
 
 
 @pytest.mark.parametrize("prec", ["f64", "f32c"])
