@@ -285,34 +285,38 @@ __global__ __launch_bounds__((SRing<PREC, RAD>::NTH), (two_resident<PREC, RAD>()
         // load and LDS store each), then NFE * NC cells one by one; without,
         // every cell one by one.  The NEE cells per field that do not fill the
         // group's threads are spread over them for all four fields together
-        // (one load under a mask at RAD = 3, not one per field).  Offsets are
-        // clamped into the padded grid for ragged tiles.
+        // (one load under a mask at RAD = 3, not one per field).  Ragged tiles
+        // clamp the places to the last column and row that the box's cells read,
+        // so that no line beyond them is fetched (a 3 x 256 x 256 slab, FP32C: 145 us
+        // with the padded grid's end as the limit, here and for the idle threads' own
+        // cells below; 102 now).
         typedef T Pair __attribute__((ext_vector_type(2)));
         constexpr int HP = HX / 2;
         constexpr int NFP = PAIRS ? (PLANE / 2) / NC : 0;   // pair slots per thread
         constexpr int CELLS0 = 2 * NFP * NC;                 // cells the pair slots cover
         constexpr int NFE = (PLANE - CELLS0) / NC, NEE = (PLANE - CELLS0) % NC;
         constexpr int NXS = (4 * NEE + NC - 1) / NC;         // left-over slots per thread
+        const int xlast = bx1 + 2 * RAD - 1, ylast = by1 + 2 * RAD - 1;  // (padded)
         unsigned poff[NFP > 0 ? NFP : 1], coff[NFE > 0 ? NFE : 1];
         const T* xptr[NXS > 0 ? NXS : 1];
         int xlds[NXS > 0 ? NXS : 1];
 #pragma unroll
         for (int k = 0; k < NFP; ++k) {
             const int p = tid + k * NC, r = p / HP, c = 2 * (p - r * HP);
-            const int px = min(x0 + c, g.mx - 2), py = min(y0 + r, g.my - 1);
+            const int px = min(x0 + c, xlast & ~1), py = min(y0 + r, ylast);
             poff[k] = (unsigned)(py * g.mx + px);
         }
 #pragma unroll
         for (int k = 0; k < NFE; ++k) {
             const int e = CELLS0 + tid + k * NC, r = e / HX, c = e - r * HX;
-            const int px = min(x0 + c, g.mx - 1), py = min(y0 + r, g.my - 1);
+            const int px = min(x0 + c, xlast), py = min(y0 + r, ylast);
             coff[k] = (unsigned)(py * g.mx + px);
         }
 #pragma unroll
         for (int k = 0; k < NXS; ++k) {
             const int i = min(tid + k * NC, 4 * NEE - 1), k4 = i / NEE;
             const int e = CELLS0 + NFE * NC + (i - k4 * NEE), r = e / HX, c = e - r * HX;
-            const int px = min(x0 + c, g.mx - 1), py = min(y0 + r, g.my - 1);
+            const int px = min(x0 + c, xlast), py = min(y0 + r, ylast);
             xptr[k] = fin + (q0 + k4) * g.fstride + (py * g.mx + px);
             xlds[k] = (q0 + k4) * PLANE + e;
         }
@@ -371,10 +375,10 @@ __global__ __launch_bounds__((SRing<PREC, RAD>::NTH), (two_resident<PREC, RAD>()
         constexpr int SOFS = 4 * NSLOT;
         auto slot_of = [](int p) { return (int)((unsigned)(p + SOFS) % (unsigned)NSLOT); };
 
-        // the thread's cell on plane bz0, clamped into the interior for the idle
+        // the thread's cell on plane bz0, clamped into the box for the idle
         // threads of ragged tiles (which load, but never store)
-        const unsigned cell0 = (unsigned)(g.interior + bz0 * g.mxy + min(y0 + ly, g.ny - 1) * g.mx +
-                                          min(x0 + lx, g.nx - 1));
+        const unsigned cell0 = (unsigned)(g.interior + bz0 * g.mxy + min(y0 + ly, by1 - 1) * g.mx +
+                                          min(x0 + lx, bx1 - 1));
 
         // ---- start of the march: planes bz0 .. bz0+RAD into the ring, and the
         // z state of plane bz0 from global memory, summed in the order in which

@@ -1,7 +1,8 @@
 """Kernels at the edges of their tiles.  Convolutions: every row length, one and
 many planes per block, both output widths, outputs that start off a vector
 boundary, infinite inputs.  Halo fill: rows of any length and start.  Reductions: rows of one and several strides, fewer
-rows than blocks, remainders.  Substep: slabs of one to four planes.  Optimizer: arrays of
+rows than blocks, remainders.  Substep: slabs of one to four planes,
+boxes of any width.  Optimizer: arrays of
 unequal sizes in one launch."""
 import threading
 
@@ -186,6 +187,37 @@ def test_thin_slabs_equal_full_substep(prec, order):
         for full, thin in zip(*got):
             assert full is None or torch.equal(full, thin)
         assert bool(torch.isfinite(got[0][0]).all())
+    S.close()
+
+
+@pytest.mark.parametrize("order", [2, 4, 6, 8])
+@pytest.mark.parametrize("prec", ["f64", "f32c", "f32"])
+@pytest.mark.parametrize("nx", [70, 69])
+def test_box_reads_its_own_surroundings_only(nx, prec, order):
+    # boxes of any width, from even and odd columns, in grids with even and odd rows (planes
+    # fetched in pairs or by cells): the full substep's bits inside, with NaN wherever the
+    # box's stencil does not reach, and nothing changed outside
+    n = (nx, 21, 12)
+    S = mhd.Solver(*n, precision=prec, order=order)
+    g = torch.Generator(device="cuda").manual_seed(order)
+    f = (torch.randn(S.layout.total_elems, generator=g, device="cuda", dtype=torch.float64) * 1e-2).to(S.torch_dtype)
+    S.halo_periodic(f)
+    old = torch.randn(f.numel(), generator=g, device="cuda").to(f) * 1e-3
+    comp = torch.randn(f.numel(), generator=g, device="cuda").to(f) * 1e-9 if prec == "f32c" else None
+    out, w, c = f.clone(), old.clone(), None if comp is None else comp.clone()
+    S.rk3_substep(1, f, out, w, c)
+    r = S.r
+    for b in ((0, 3, 0, 21, 0, 12), (nx - 1, nx, 0, 21, 2, 12), (2, 35, 4, 13, 1, 4), (33, 66, 20, 21, 0, 12), (32, 64, 8, 16, 5, 6), (0, nx, 0, 21, 0, 12)):
+        inside = lambda t, k=0: S.grid_view(t)[:, r + b[4] - k:r + b[5] + k, r + b[2] - k:r + b[3] + k, r + b[0] - k:r + b[1] + k]  # noqa: E731
+        around = torch.full_like(f, float("nan"))
+        inside(around, r).copy_(inside(f, r))
+        got = [torch.full_like(f, 7.0), old.clone(), None if comp is None else comp.clone()]
+        want = [torch.full_like(f, 7.0), old.clone(), None if comp is None else comp.clone()]
+        S.rk3_substep_box(1, b, around, *got)
+        for a, e, full in zip(got, want, (out, w, c)):
+            if e is not None:
+                inside(e).copy_(inside(full))
+                assert torch.equal(a, e), b
     S.close()
 
 
