@@ -108,11 +108,19 @@ constexpr size_t ring_bytes()
 // ask for more than half of the 160 KB where the ring is smaller.
 template <int PREC, int RAD>
 constexpr bool two_resident() { return PREC == MHD_F32 && RAD <= 3; }
+// Whether two share one only where the tiles are ragged (see ragged_tiles).
+template <int PREC, int RAD>
+constexpr bool two_if_ragged() { return PREC == MHD_F32C && RAD == 1; }
+template <int PREC, int RAD>
+constexpr size_t lds_needed()
+{
+    return ring_bytes<PREC, RAD>() +
+           sizeof(typename Prec<PREC>::Rt) * (nxf<PREC>() + nxm<PREC>()) * SRing<PREC, RAD>::NC;
+}
 template <int PREC, int RAD>
 constexpr size_t lds_bytes()
 {
-    constexpr size_t need = ring_bytes<PREC, RAD>() +
-                            sizeof(typename Prec<PREC>::Rt) * (nxf<PREC>() + nxm<PREC>()) * SRing<PREC, RAD>::NC;
+    constexpr size_t need = lds_needed<PREC, RAD>();
     return two_resident<PREC, RAD>() || need > 84 * 1024 ? need : 84 * 1024;
 }
 
@@ -792,13 +800,32 @@ __global__ __launch_bounds__((SRing<PREC, RAD>::NTH), (two_resident<PREC, RAD>()
         march(std::integral_constant<int, 1>{});
 }
 
+// Whether the boxes fill less than 0.8 of their tiles' columns.  Such tiles ask less
+// of the memory system, latency bounds the march, and a second workgroup per CU pays
+// where whole tiles lose by it.  us per step, FP32C second order, with one and two
+// (share of the columns): 16 x 500 x 500 925 -> 812 (0.50), 40 x 400 x 300 1050 -> 986 (0.63),
+// 100^3 159 -> 144 (0.75), 300 x 20 x 400 461 -> 441 (0.78); 200^3 1338 -> 1402 (0.89),
+// 256^3 2409 -> 2545 (1).
+bool ragged_tiles(const Box* bx, int nbox, int tx, int ty)
+{
+    int64_t cells = 0, tiles = 0;
+    for (int k = 0; k < nbox; ++k) {
+        const int64_t nx = bx[k].x1 - bx[k].x0, ny = bx[k].y1 - bx[k].y0, nz = bx[k].z1 - bx[k].z0;
+        cells += nx * ny * nz;
+        tiles += (nx + tx - 1) / tx * ((ny + ty - 1) / ty) * nz;
+    }
+    return 10 * cells < 8 * tiles * tx * ty;
+}
+
 template <int PREC, int RAD>
 hipError_t launch_one(const Grid& g, const Phys& P, const Phys* P_dev, const Box* bx, int nbox,
                       int s, const void* f_in, void* f_out, void* w, void* comp, double dt,
                       hipStream_t st)
 {
     using T = typename Prec<PREC>::T;
-    constexpr size_t lds = lds_bytes<PREC, RAD>();
+    const bool two = two_if_ragged<PREC, RAD>() &&
+                     ragged_tiles(bx, nbox, SRing<PREC, RAD>::TX, SRing<PREC, RAD>::TY);
+    const size_t lds = two ? lds_needed<PREC, RAD>() : lds_bytes<PREC, RAD>();
     // pair fetches, where they measured faster: FP64 (9.51 -> 9.36 ms per substep
     // before the loads were spread), FP32 storage up to order 6 (512^3 step
     // 21.3 -> 20.8 ms with compensation, 15.5 -> 14.5 plain), not at order 8
@@ -808,7 +835,7 @@ hipError_t launch_one(const Grid& g, const Phys& P, const Phys* P_dev, const Box
     // limit of every variant, and the workgroups resident at once (a round)
     struct Setup {
         hipError_t err;
-        int round;
+        int round, round_two;
     };
     static const Setup setup = []() -> Setup {
         const void* kernels[4] = {(const void*)k_rk3_split<PREC, RAD, false, false>,
@@ -822,17 +849,20 @@ hipError_t launch_one(const Grid& g, const Phys& P, const Phys* P_dev, const Box
         for (int k = 0; k < 4 && e == hipSuccess; ++k)
             if (kernels[k])
                 e = hipFuncSetAttribute(kernels[k], hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        (int)lds);
-        int per_cu = 0, dev = 0, cus = 0;
+                                        (int)lds_bytes<PREC, RAD>());
+        int per_cu = 0, two_per_cu = 0, dev = 0, cus = 0;
         if (e == hipSuccess)
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &per_cu, k_rk3_split<PREC, RAD, false, false>, SRing<PREC, RAD>::NTH, lds);
+            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_rk3_split<PREC, RAD, false, false>,
+                                                             SRing<PREC, RAD>::NTH, lds_bytes<PREC, RAD>());
+        if (e == hipSuccess && two_if_ragged<PREC, RAD>())
+            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&two_per_cu, k_rk3_split<PREC, RAD, false, false>,
+                                                             SRing<PREC, RAD>::NTH, lds_needed<PREC, RAD>());
         if (e == hipSuccess) e = hipGetDevice(&dev);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        return Setup{e, per_cu * cus};
+        return Setup{e, per_cu * cus, min(two_per_cu, 2) * cus};
     }();
     if (setup.err != hipSuccess) return setup.err;
-    const int round = setup.round;
+    const int round = two ? setup.round_two : setup.round;
     const TilePlan plan =
         plan_tiles(bx, nbox, SRing<PREC, RAD>::TX, SRing<PREC, RAD>::TY, round);
     Scales<RAD> sc{};
