@@ -124,6 +124,17 @@ constexpr int CONV_CELLS = 256;  // cells per plane per block
 template <int CIN>
 constexpr int conv_cp() { return CIN == 32 ? CIN + 8 : CIN; }
 
+// Whether a plane's results pass through LDS, from where the block stores them in whole
+// cache lines: 32 FP32 channels are a line per cell, of which a wave has half, and with
+// 8 input channels nothing else takes as long as the stores.  Non-temporal ones: outputs
+// beyond the 256 MB that the memory-side cache holds gain by it and smaller ones lose nothing.  us for 8 -> 32
+// channels, FP32, of 2, 4, 6, 8 and 16 x 64^3 cells: half lines 17.2, 29.7, 65, 86, 203; whole lines
+// 16.5, 27.8, 59, 92, 184; non-temporal 17.8, 28.5, 60, 55, 104.  (Waves with all channels of 32 cells
+// and one store per channel, the kernel before: 17.7, 30.2, 62, 72, 154.)
+template <int CIN, int MODE, int COUT>
+constexpr bool conv_staged() { return CIN == 8 && MODE == 1 && COUT == 32; }
+constexpr int STAGE_CP = 36;  // floats per cell there
+
 // DPP moves within rows of 16 lanes (one tile of cells): lane x takes lane x -+ 1,
 // the first (last) lane takes the last (first) lane of the tile before (after).
 __device__ __forceinline__ float from_left(float v, float left_tile)
@@ -227,6 +238,8 @@ __global__ __launch_bounds__(CONV_THR) void k_conv(const uint16_t* __restrict__ 
         return ((size_t)b * n3 + ((size_t)(z0 + p) << (2 * LOGN)) + ((size_t)y0 << LOGN)) * COUT;
     };
     const unsigned lane_out = (unsigned)((mbase + c16) * COUT + ch);
+    constexpr bool STAGED = conv_staged<CIN, MODE, COUT>();
+    float* stage = reinterpret_cast<float*>(lx + 4 * SLOT + 8);  // [2][CONV_CELLS][STAGE_CP]
     floatx4 res[4];
     u16x4 zp[4];
     auto finish = [&](int p) {  // plane z0 + p's results, four channels per lane and tile
@@ -247,11 +260,25 @@ __global__ __launch_bounds__(CONV_THR) void k_conv(const uint16_t* __restrict__ 
                     a[i] = f2bf(v[i] * gelu_grad(bf2f(zp[j][i])));
                 }
             }
-            if constexpr (MODE == 1)
+            if constexpr (STAGED)
+                *reinterpret_cast<floatx4*>(stage + ((p & 1) * CONV_CELLS + mbase + 16 * j + c16) * STAGE_CP + ch) = v;
+            else if constexpr (MODE == 1)
                 *reinterpret_cast<f32x4u*>(outf + at + o) = v;
             else
                 *reinterpret_cast<u16x4*>(out0 + at + o) = a;
             if constexpr (MODE == 0) *reinterpret_cast<u16x4*>(out1 + at + o) = g;
+        }
+    };
+    auto flush = [&](int p) {  // plane z0 + p's staged results, a barrier after finish(p)
+        if constexpr (STAGED) {
+            float* out = outf + out_plane(p);
+            const float* st = stage + (p & 1) * CONV_CELLS * STAGE_CP;
+#pragma unroll
+            for (int k = 0; k < CONV_CELLS * 8 / CONV_THR; ++k) {
+                const int i = tid + k * CONV_THR;
+                const f32x4u v = *reinterpret_cast<const floatx4*>(st + (i >> 3) * STAGE_CP + 4 * (i & 7));
+                __builtin_nontemporal_store(v, reinterpret_cast<f32x4u*>(out + 4 * i));
+            }
         }
     };
     int rbase[4];  // tile j's cell of this lane in the ring plane, row dy = -1
@@ -335,15 +362,20 @@ __global__ __launch_bounds__(CONV_THR) void k_conv(const uint16_t* __restrict__ 
     turn(0);
     if (ch0 >= COUT) {  // no output channels: this wave only moves planes
         for (int p = 1; p < nz; ++p) turn(p);
-    } else if (CIN == 32 && wv < 4) {
+    } else if (STAGED || (CIN == 32 && wv < 4)) {
         load_zp(0);
         products(0);
         finish(0);
         for (int p = 1; p < nz; ++p) {
             turn(p);
+            flush(p - 1);
             load_zp(p);
             products(p);
             finish(p);
+        }
+        if constexpr (STAGED) {
+            __syncthreads();
+            flush(nz - 1);
         }
     } else {
         products(0);
@@ -921,9 +953,12 @@ void conv_chunks(int n, int batch, int& columns, int& nch, int& zc)
     nch = (n + zc - 1) / zc;
 }
 
-size_t conv_lds(int cin, int n)
+template <int CIN, int MODE, int LOGN, int COUT>
+constexpr size_t conv_lds()
 {
-    return 2 * (4 * (CONV_CELLS / n + 2) * n * (cin == 32 ? conv_cp<32>() : conv_cp<8>()) + 8);
+    constexpr int n = 1 << LOGN;
+    return 2 * (4 * (CONV_CELLS / n + 2) * n * conv_cp<CIN>() + 8) +
+           (conv_staged<CIN, MODE, COUT>() ? 4 * 2 * CONV_CELLS * STAGE_CP : 0);
 }
 
 template <int CIN, int MODE, int LOGN, int COUT>
@@ -934,12 +969,12 @@ hipError_t launch_conv_n(const uint16_t* x, const uint16_t* w, const float* bias
     // once per instantiation (thread-safe static initialisation)
     static const hipError_t attr =
         hipFuncSetAttribute((const void*)k_conv<CIN, MODE, LOGN, COUT>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)conv_lds(CIN, 1 << LOGN));
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)conv_lds<CIN, MODE, LOGN, COUT>());
     if (attr != hipSuccess) return attr;
     int columns, nch, zc;
     conv_chunks(1 << LOGN, batch, columns, nch, zc);
     hipLaunchKernelGGL((k_conv<CIN, MODE, LOGN, COUT>), dim3(columns * nch), dim3(CONV_THR),
-                       conv_lds(CIN, 1 << LOGN), st, x, w, bias, zp, nch, zc, o0, o1, of);
+                       (conv_lds<CIN, MODE, LOGN, COUT>()), st, x, w, bias, zp, nch, zc, o0, o1, of);
     return hipGetLastError();
 }
 
