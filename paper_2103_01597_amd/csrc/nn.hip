@@ -672,40 +672,41 @@ __global__ __launch_bounds__(NTHR) void k_wgrad_reduce(const float* __restrict__
 // Several arrays in one launch: launches, not work, are what a training step's
 // updates of six small arrays and preparations of three layers cost: nine
 // launches, two now (backward pass at 4 x 64^3 308 -> 298 us).  Block b serves the part whose blocks begin at
-// or before b (uniform).
+// or before b (uniform).  N: 1 where there is one array, which needs no search and few
+// kernel arguments, else MAX_PARTS.
 constexpr int MAX_PARTS = 8;
-template <typename P>
+template <typename P, int N>
 struct Parts {
-    P part[MAX_PARTS];
-    int first[MAX_PARTS + 1];  // first block of each part, then their number
+    P part[N];
+    int first[N];  // first block of each part
 };
-template <typename P>
-__device__ __forceinline__ P part_of_block(const Parts<P>& s, int& block)
+template <typename P, int N>
+__device__ __forceinline__ P part_of_block(const Parts<P, N>& s, int& block)
 {
     int k = 0;
 #pragma unroll
-    for (int q = 1; q < MAX_PARTS; ++q) k += (int)blockIdx.x >= s.first[q];
+    for (int q = 1; q < N; ++q) k += (int)blockIdx.x >= s.first[q];
     block = blockIdx.x - s.first[k];
     return s.part[k];
 }
 // blocks(part) blocks each; parts past count get none
-template <typename P, typename F>
-Parts<P> make_parts(const P* parts, int count, F blocks)
+template <int N, typename P, typename F>
+Parts<P, N> make_parts(const P* parts, int count, F blocks)
 {
-    Parts<P> s{};
+    Parts<P, N> s{};
     int at = 0;
-    for (int k = 0; k < MAX_PARTS; ++k) {
+    for (int k = 0; k < N; ++k) {
         s.first[k] = at;
         if (k < count) {
             s.part[k] = parts[k];
             at += blocks(parts[k]);
         }
     }
-    s.first[MAX_PARTS] = at;
     return s;
 }
 
-__global__ void k_prepare_weights(Parts<mhdnn_weights_part> s)
+template <int N>
+__global__ void k_prepare_weights(Parts<mhdnn_weights_part, N> s)
 {
     int block;
     const mhdnn_weights_part a = part_of_block(s, block);
@@ -910,19 +911,21 @@ __global__ void k_stats_final(const double* __restrict__ partials, double count,
     out[q] = root ? sqrt(s) : s;
 }
 
-__global__ void k_adam(Parts<mhdnn_adam_part> s, float lr, float b1, float b2, float eps, float c1,
+template <int N>
+__global__ void k_adam(Parts<mhdnn_adam_part, N> s, float lr, float b1, float b2, float eps, float c1,
                        float c2)
 {
     int block;
     const mhdnn_adam_part a = part_of_block(s, block);
     const int64_t i = (int64_t)block * blockDim.x + threadIdx.x;
     if (i >= a.n) return;
-    const float gi = a.g[i];
-    const float mi = b1 * a.m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * a.v[i] + (1.0f - b2) * gi * gi;
+    // (all four in flight before the first store, which the compiler must take to alias them)
+    const float gi = a.g[i], m0 = a.m[i], v0 = a.v[i], p0 = a.p[i];
+    const float mi = b1 * m0 + (1.0f - b1) * gi;
+    const float vi = b2 * v0 + (1.0f - b2) * gi * gi;
     a.m[i] = mi;
     a.v[i] = vi;
-    a.p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    a.p[i] = p0 - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
 int ilog2(int n)
@@ -1195,11 +1198,17 @@ int mhdnn_prepare_weights_parts(const mhdnn_weights_part* parts, int32_t count, 
             return MHD_ERR_INVALID;
     }
     if (count == 0) return MHD_OK;
-    const auto set = make_parts(parts, count, [](const mhdnn_weights_part& a) {
+    int total = 0;
+    auto blocks = [](const mhdnn_weights_part& a) {
         return (32 * 27 * (a.cin > a.cout ? a.cin : a.cout) + 255) / 256;
-    });
-    hipLaunchKernelGGL(k_prepare_weights, dim3(set.first[MAX_PARTS]), dim3(256), 0,
-                       (hipStream_t)stream, set);
+    };
+    for (int k = 0; k < count; ++k) total += blocks(parts[k]);
+    hipStream_t st = (hipStream_t)stream;
+    if (count == 1)
+        hipLaunchKernelGGL(k_prepare_weights<1>, dim3(total), dim3(256), 0, st, make_parts<1>(parts, count, blocks));
+    else
+        hipLaunchKernelGGL(k_prepare_weights<MAX_PARTS>, dim3(total), dim3(256), 0, st,
+                           make_parts<MAX_PARTS>(parts, count, blocks));
     return status(hipGetLastError());
 }
 
@@ -1260,20 +1269,24 @@ int mhdnn_adam_parts(const mhdnn_adam_part* parts, int32_t count, float lr, floa
                      float eps, int32_t t, void* stream)
 {
     if (!parts || count < 0 || count > MAX_PARTS || t < 1) return MHD_ERR_INVALID;
-    int64_t blocks = 0;
+    auto blocks = [](const mhdnn_adam_part& a) { return a.n / 256 + (a.n % 256 != 0); };
+    int64_t total = 0;
     for (int k = 0; k < count; ++k) {
         const mhdnn_adam_part& a = parts[k];
         if (!a.p || !a.g || !a.m || !a.v || a.n < 0) return MHD_ERR_INVALID;
-        blocks += a.n / 256 + (a.n % 256 != 0);
-        if (blocks > INT32_MAX) return MHD_ERR_INVALID;  // more than 2 TB of parameters
+        total += blocks(a);
+        if (total > INT32_MAX) return MHD_ERR_INVALID;  // more than 2 TB of parameters
     }
-    if (blocks == 0) return MHD_OK;
+    if (total == 0) return MHD_OK;
     const float c1 = 1.0f - powf(b1, (float)t), c2 = 1.0f - powf(b2, (float)t);
-    const auto set = make_parts(parts, count, [](const mhdnn_adam_part& a) {
-        return (int)(a.n / 256 + (a.n % 256 != 0));
-    });
-    hipLaunchKernelGGL(k_adam, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, set, lr,
-                       b1, b2, eps, c1, c2);
+    const dim3 grid((unsigned)total);
+    hipStream_t st = (hipStream_t)stream;
+    if (count == 1)
+        hipLaunchKernelGGL(k_adam<1>, grid, dim3(256), 0, st, make_parts<1>(parts, count, blocks), lr, b1, b2,
+                           eps, c1, c2);
+    else
+        hipLaunchKernelGGL(k_adam<MAX_PARTS>, grid, dim3(256), 0, st, make_parts<MAX_PARTS>(parts, count, blocks),
+                           lr, b1, b2, eps, c1, c2);
     return status(hipGetLastError());
 }
 
