@@ -130,11 +130,15 @@ def prepare_weights(w, cin, cout, w_pad, wt_pad=None, stream=None):
                                                               _p(wt_pad), _st(stream)))
 
 
+MAX_PARTS = 8  # arrays that one launch takes
+
+
 def prepare_weights_parts(parts, stream=None):
-    """parts: up to 8 of (w, cin, cout, w_pad, wt_pad or None)."""
-    arr = (WeightsPart * max(len(parts), 1))(*[WeightsPart(_p(w), _p(wp), _p(wt), cin, cout)
-                                       for w, cin, cout, wp, wt in parts])
-    _chk("mhdnn_prepare_weights_parts", lib().mhdnn_prepare_weights_parts(arr, len(parts), _st(stream)))
+    """parts: any number of (w, cin, cout, w_pad, wt_pad or None), MAX_PARTS a launch."""
+    for k in range(0, len(parts), MAX_PARTS):
+        some = [WeightsPart(_p(w), _p(wp), _p(wt), cin, cout) for w, cin, cout, wp, wt in parts[k:k + MAX_PARTS]]
+        _chk("mhdnn_prepare_weights_parts", lib().mhdnn_prepare_weights_parts(
+            (WeightsPart * len(some))(*some), len(some), _st(stream)))
 
 
 def mse(y, target, tscale, n, batch, dy, partials, stream=None):
@@ -166,10 +170,11 @@ def adam(p, g, m, v, lr, t, b1=0.9, b2=0.999, eps=1e-8, stream=None):
 
 
 def adam_parts(parts, lr, t, b1=0.9, b2=0.999, eps=1e-8, stream=None):
-    """parts: up to 8 of (p, g, m, v), disjoint."""
-    arr = (AdamPart * max(len(parts), 1))(*[AdamPart(_p(p), _p(g), _p(m), _p(v), p.numel())
-                                    for p, g, m, v in parts])
-    _chk("mhdnn_adam_parts", lib().mhdnn_adam_parts(arr, len(parts), lr, b1, b2, eps, t, _st(stream)))
+    """parts: any number of (p, g, m, v), disjoint, MAX_PARTS a launch."""
+    for k in range(0, len(parts), MAX_PARTS):
+        some = [AdamPart(_p(p), _p(g), _p(m), _p(v), p.numel()) for p, g, m, v in parts[k:k + MAX_PARTS]]
+        _chk("mhdnn_adam_parts", lib().mhdnn_adam_parts(
+            (AdamPart * len(some))(*some), len(some), lr, b1, b2, eps, t, _st(stream)))
 
 
 def apply(solver, fields, comp, y, scale, guard=None, stream=None):

@@ -244,3 +244,36 @@ def test_updates_in_one_launch_equal_one_by_one(sizes):
         flip = torch.zeros(32, 27, cout, device="cuda")
         flip[:cin] = w.flip(1).permute(2, 1, 0)
         assert torch.equal(wt.view(32, 27, cout), flip.to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("sizes", [(3, 0, 300), (0, 5, 0, 0, 257), (256, 0), (0, 0), (1,) * 8, (40,) * 9, (7, 0, 300) * 6])
+def test_updates_of_any_number_of_arrays(sizes):
+    # arrays without elements (at an address of their own) between others, and more arrays
+    # than one launch takes: as many calls of one array
+    g = torch.Generator(device="cuda").manual_seed(len(sizes))
+    parts = [tuple(torch.rand(n + 1, generator=g, device="cuda") for _ in range(4)) for n in sizes]
+    alone = [tuple(t.clone() for t in q) for q in parts]
+    rows = (nn.AdamPart * len(sizes))(*[nn.AdamPart(*[t.data_ptr() for t in q], n) for q, n in zip(parts, sizes)])
+    if len(sizes) <= nn.MAX_PARTS:
+        nn._chk("adam", nn.lib().mhdnn_adam_parts(rows, len(sizes), 1e-3, 0.9, 0.999, 1e-8, 1, nn._st()))
+    else:
+        nn.adam_parts([tuple(t[:n] if n else t[:1] for t in q) for q, n in zip(parts, sizes) if n], 1e-3, 1)
+    for q, n in zip(alone, sizes):
+        if n:
+            nn.adam(*[t[:n] for t in q], 1e-3, 1)
+    for a, b in zip(parts, alone):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+def test_closure_of_more_layers_than_one_launch_takes(monkeypatch):
+    # inference takes any depth: the layers' weights are prepared however many there are
+    deep = ((8, 32, True),) + ((32, 32, True),) * 8 + ((32, 8, False),)
+    monkeypatch.setattr(nn, "LAYERS", deep)
+    net = nn.Closure(seed=1)
+    for (cin, cout, _), w, wp in zip(deep, net.w, net.w_pad):
+        assert torch.equal(wp.view(32, 27, cin)[:cout], w.to(torch.bfloat16))
+    x = torch.randn(16 ** 3 * 8, device="cuda").to(torch.bfloat16)
+    y, _ = net.forward(x, 16, 1)
+    assert bool(torch.isfinite(y).all())
+    net.step([torch.ones_like(p) for p in net.params], 1e-3)
+    assert all(bool((p != 0).any()) for p in net.params)
