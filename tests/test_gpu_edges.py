@@ -221,6 +221,35 @@ def test_box_reads_its_own_surroundings_only(nx, prec, order):
     S.close()
 
 
+@pytest.mark.parametrize("n,prec,order", [((16, 16, 16), "f64", 6), ((40, 33, 20), "f32c", 2), ((64, 24, 30), "f32", 8)])
+def test_captured_steps_equal_eager_ones(n, prec, order):
+    # two steps recorded by the caller and replayed, with eager work and waits between
+    # the replays: the same bits each time
+    S = mhd.Solver(*n, precision=prec, order=order)
+    g = torch.Generator(device="cuda").manual_seed(order)
+    f0 = (torch.randn(S.layout.total_elems, generator=g, device="cuda", dtype=torch.float64) * 1e-2).to(S.torch_dtype)
+
+    def state():
+        return [f0.clone(), S.zeros()], S.zeros(), S.zeros() if prec == "f32c" else None
+
+    (fe, we, ce), (fc, wc, cc) = state(), state()
+    S.step(fe, 0, we, ce, 1e-3, 2)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        assert S.step(fc, 0, wc, cc, 1e-3, 2) == 0
+    assert torch.equal(fc[0], f0)  # recorded, not run
+    for _ in range(4):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(S.interior_view(fc[0]), S.interior_view(fe[0])) and torch.equal(wc, we)
+        assert ce is None or torch.equal(cc, ce)
+        assert S.reduce(fc[0], 1, "maxabs") > 0
+        S.step(fe, 0, we, ce, 1e-3, 2)
+    S.close()
+
+
 @pytest.mark.parametrize("sizes", [(1,), (256, 1), (6912, 32, 27648, 0, 6912, 8), (257, 255, 256, 1, 2, 3, 4, 5)])
 def test_updates_in_one_launch_equal_one_by_one(sizes):
     g = torch.Generator(device="cuda").manual_seed(len(sizes))
