@@ -43,9 +43,10 @@ __device__ __forceinline__ int quotient(int a, int d, float inv)
 // us, FP64, 512^3 / 256^3 / 32^3 in a step (three fills and three substeps) / 30000 x 8 x 8:
 //   three launches (columns, then whole rows and planes)     258 / 50.9 / - / 73
 //   one launch, field by field, columns beside the rows,
-//   rows by lanes of their own, cell by cell                 271 / 48.2 / 45.3 / 102
-//   units, four per lane, rows before columns, field by field 254 / 47.6 / 47.9 / 69
-//   units, one per lane, the fields interleaved (now)        247 / 47.0 / 43.1 / 69
+//   rows by lanes of their own, cell by cell                 271 / 48.2 / 43.4 / 102
+//   units, four per lane, rows before columns, field by field 254 / 47.6 / 46.9 / 69
+//   units, one per lane, the fields interleaved (now)        246 / 47.4 / 42.5 / 68
+// (at 512^3 in a step, where the substep leaves lines in the caches: 247 -> 219)
 constexpr int HX_ROWS = 32, HALO_THR = 256;
 
 template <typename E, bool THIN>

@@ -97,8 +97,8 @@ constexpr int NTHR = 256;
 // consecutive output channels of a cell and stores them in one access.
 //
 // The bound is the instruction stream of a wave (LDS fragment reads, products,
-// the rounding and GELU of the results), not memory (0.2 of the time at the
-// copy rate).  So:
+// the rounding and GELU of the results) before memory (the bytes alone would take
+// 0.45 to 0.48 of the time at the copy rate).  So:
 //   * one fragment read serves the three taps along x: each has an accumulator
 //     of its own over the unshifted cells, and the three are shifted and added
 //     at the plane's end by DPP moves inside the rows of 16 lanes.  That is 9

@@ -46,14 +46,17 @@
 // clocks) while the earlier one waited at the barrier: 9.1 ms per substep.
 // Spread over the plane, with 9 values handed over instead of 17, each step's
 // LDS reads issued ahead of the step before it, and the march started without
-// warm-up planes, it takes 7.9 ms.  What is left is shared by the memory
-// system and the power limit: without the stencil's LDS reads it would take
-// 7.4, without its arithmetic 7.7 ms, and the clock is down to 2.0 GHz.  A
-// third wave per SIMD (three groups: u, A, and lnrho with s) changes nothing
+// warm-up planes, it takes 7.9 ms.  No single unit is full: of the clocks (2.05 GHz
+// on average) the SIMDs issue VALU instructions in 45%, the LDS is busy in 49% and
+// the address units in 39%, and waves wait for an instruction 22% of their time.
+// Leaving out the stencil's LDS reads alone gives 7.4 ms, its arithmetic alone 7.7.
+// A third wave per SIMD (three groups: u, A, and lnrho with s) changes nothing
 // (7.8-7.9 ms), nor do wave priorities; non-temporal stores cost 6%.
-// With FP32 storage one thread per cell for all 8 fields, two workgroups to a
-// CU, took 22.6 ms per step at 512^3, sixth order (21.8 at orders 2 and 4); the
-// two groups take 20.2 (18.6, 19.3) although only one workgroup is resident.
+// FP32 storage with compensation is nearest to VALU issue (65% of the clocks): the
+// second derivatives' sums are FP64 and their inputs FP32.  One thread per cell for
+// all 8 fields, two workgroups to a CU, took 22.0 ms per step at 512^3, halo fills
+// included, sixth order (21.8 and 21.6 at second and fourth); the two groups take 20.6
+// (18.5, 19.4) although only one workgroup is resident.
 #pragma once
 
 #include <type_traits>
@@ -73,6 +76,9 @@ namespace {
 // values 8.2, 9 values 7.9 ms per substep).  With its terms handed over like
 // those of FP64, one step of FP32C at 512^3 changed 40% of the register values
 // by a rounding; now four of the eight fields keep every bit.
+// What FP64 gives up: the two halves of the pressure gradient meet after the
+// hand-over, so where they cancel exactly (s = -lnrho with cp = 1) the rounding of
+// one product is left, 2e-16 of it, and not zero.
 template <int PREC>
 constexpr bool physics_late() { return PREC != MHD_F64; }
 template <int PREC>
@@ -101,8 +107,9 @@ constexpr size_t ring_bytes()
     return sizeof(typename Prec<PREC>::T) * SRing<PREC, RAD>::NSLOT * SRing<PREC, RAD>::SLOT;
 }
 // Whether two workgroups share a CU: plain FP32 up to r = 3, whose rings and
-// registers (124, held to 128 at r = 2) allow it.  us per step at 256^3 with one
-// and two: orders 2, 4, 6 1890 -> 1735, 1873 -> 1830, 1973 -> 1878.
+// registers allow it (82, 128 and 124-128; the 128 at r = 2 leave one pointer of
+// group M in scratch memory, read back once per plane).  us per step at 256^3 with
+// one and two: orders 2, 4, 6 1890 -> 1735, 1873 -> 1830, 1973 -> 1878.
 // The other precisions fit two at r = 1 only and lose by it, as the halo reads
 // of two tiles find less in L2: FP64 3150 -> 3240, FP32C 2440 -> 2567.  They
 // ask for more than half of the 160 KB where the ring is smaller.
@@ -828,7 +835,8 @@ hipError_t launch_one(const Grid& g, const Phys& P, const Phys* P_dev, const Box
     const size_t lds = two ? lds_needed<PREC, RAD>() : lds_bytes<PREC, RAD>();
     // pair fetches, where they measured faster: FP64 (9.51 -> 9.36 ms per substep
     // before the loads were spread), FP32 storage up to order 6 (512^3 step
-    // 21.3 -> 20.8 ms with compensation, 15.5 -> 14.5 plain), not at order 8
+    // 21.3 -> 20.8 ms with compensation, 15.5 -> 14.5 plain, both before the physics
+    // moved behind the hand-over; 20.6 and 15.0 since), not at order 8
     // (256^3 step 3.05 -> 3.10 ms)
     constexpr bool PAIRS_OK = PREC == MHD_F64 || RAD < 4;
     // once per instantiation (thread-safe static initialisation): the LDS
